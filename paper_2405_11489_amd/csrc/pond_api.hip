@@ -76,6 +76,7 @@ pond_status read_counters(pond_ctx *c, DevCounters *out) {
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(counters)");
     e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+    out->fold();
     return POND_OK;
 }
 
@@ -140,7 +141,7 @@ static long long tiles_of(const pond_params &p, int tx, int ty) {
 // ones).  The FP32 D2Q16 kernels with the shared x-pass run two waves per SIMD
 // at either block size, so they keep 32 x 8 (2048^2 quadrants: 1.13 against
 // 1.32 ms per step with 32 x 16; 512^2 Mach 2: 0.153 against 0.159 ms).
-pond_tuning default_tuning(const pond_params &p) {
+pond_tuning default_tuning(const pond_params &p, int reach) {
     pond_tuning t;
     t.kernel = POND_KERNEL_TILED;
     const bool dbl = p.precision == POND_PREC_FP64;
@@ -164,9 +165,15 @@ pond_tuning default_tuning(const pond_params &p) {
             }
         }
     }
+    // flows whose stencils reach two nodes at most (cold, slow): small tiles, which
+    // carry little more halo there and end their waves sooner where the
+    // predictor-corrector work varies (2048^2 quadrants, FP32: 0.70 ms per step
+    // against 0.80 with 32 x 8; 1024^2, FP64: 0.58 against 0.69)
+    const bool small = reach > 0 && reach <= 2 && p.ny >= 16;
     // D2Q25: square tiles, whose source regions carry less halo per node (512^2
     // Mach 2: 545 against 495 MLUPS with 32 x 8)
     if (p.lattice == POND_LATTICE_D2Q25 && p.ny >= 16) t.tile = POND_TILE_16x16;
+    if (small) t.tile = POND_TILE_16x8;
     t.lds_nodes =
         default_lds_nodes(t.tile, p.precision == POND_PREC_FP64, p.interp_points, p.split,
                           p.lattice);
@@ -174,7 +181,7 @@ pond_tuning default_tuning(const pond_params &p) {
     // block per CU holding its whole 40 x 16 source region beats two blocks
     // that fall back to HBM for part of the taps (527 vs 323 MLUPS); a 32 x 16
     // block fills one CU by its registers alone
-    if (dbl && p.ny >= 8 && p.lattice == POND_LATTICE_D2Q16)
+    if (dbl && p.ny >= 8 && !small && p.lattice == POND_LATTICE_D2Q16)
         t.lds_nodes = lds_nodes_for_blocks(1, true);
     t.batch_tile_width = 0;
     return t;
@@ -251,6 +258,7 @@ void pond::fill_step_args(const pond_params &p, StepArgs &a) {
         a.wall_T[k] = p.wall_T[k];
     }
     a.cv = 1.0 / (p.gamma - 1.0);
+    a.rcv = 1.0 / a.cv;
     a.uref_x = a.uref_y = 0.0;
 }
 
@@ -348,13 +356,15 @@ pond_status check_unbatched(const pond_ctx *c) {
 }
 
 // Stencil reach of the frame just loaded (from cnt->partial[3]) and, unless the
-// tuning was set explicitly, the autotuned configuration of the context's class.
+// tuning was set explicitly, the autotuned configuration of the context's class or
+// the default for that reach.
 pond_status finish_init(pond_ctx *c, const DevCounters &h) {
     const double r = std::ceil(h.partial[3]);
     c->reach = r > 1e6 ? 1000000 : int(r);
+    if (c->user_tuned) return POND_OK;
     pond_tuning t;
-    if (!c->user_tuned && tuning_cache_lookup(c, &t)) return apply_tuning(c, t);
-    return POND_OK;
+    if (!tuning_cache_lookup(c, &t)) t = default_tuning(c->p, c->reach);
+    return apply_tuning(c, t);
 }
 
 pond_status set_reference_from_counters(pond_ctx *c) {

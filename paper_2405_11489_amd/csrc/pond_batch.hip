@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(
     const BatchMember *__restrict__ mem, const int *__restrict__ tile_off, int nmem, int cap,
     int flip, int ntiles) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ int red[4 * red_slots<Shape256::kThreads>()];
+    __shared__ int red[bound_slots<Shape256::kThreads>()];
 #if POND_BATCH_PERSISTENT
     // the grid has at least 8 blocks, so every XCD has one
     const int b = int(blockIdx.x), nb = int(gridDim.x), x = b % 8;
@@ -669,7 +669,7 @@ pond_status pond_autotune(pond_ctx *c, int steps, pond_tuning *out) {
         tiles = {POND_TILE_64x1, POND_TILE_256x1};
         widths = {256};
     } else {
-        tiles = {default_tuning(c->p).tile, POND_TILE_32x8, POND_TILE_16x16, POND_TILE_16x8};
+        tiles = {default_tuning(c->p, c->reach).tile, POND_TILE_32x8, POND_TILE_16x16, POND_TILE_16x8};
         if (c->p.lattice == POND_LATTICE_D2Q16) tiles.push_back(POND_TILE_32x16);
         // one-wave blocks: each wave frees its CU share as soon as it is done, which
         // pays where the predictor-corrector work varies from wave to wave (shocks:

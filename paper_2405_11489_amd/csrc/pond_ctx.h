@@ -67,8 +67,9 @@ int lds_nodes_for_blocks(int blocks_per_cu, bool dbl, int lattice = 16);
 // LDS nodes per block of the tiled kernel's default share for a tile shape.
 int default_lds_nodes(int tile, bool dbl, int np, int split, int lattice);
 // Default launch configuration of a context with these parameters (on the
-// current device).
-pond_tuning default_tuning(const pond_params &p);
+// current device); reach: the stencil reach of its initial frame in nodes, 0 if
+// it is not known.
+pond_tuning default_tuning(const pond_params &p, int reach = 0);
 
 // POND_OK, or the status and message (pond_last_error) of the first invalid or
 // unsupported parameter.  Touches no device.

@@ -34,16 +34,10 @@ constexpr int kQ = 16;       // D2Q16 velocities, i = 4a + b, c_i = (c1(a), c1(b
 constexpr int kNM = 10;      // moments / Grad coefficients per distribution
 
 // Per-velocity constants, i = 4a + b with c_i = (c1(a), c1(b)).
-//  recon[i][k]: weights of the N = 3 Grad reconstruction (Eq.
-//    gradGeneralTransform with rT_L = 1) on the normalised central moments m_k
-//    (same ordering as the moments): pop_i = sum_k recon[i][k] m_k, from the
-//    Hermite coefficients a0 = m00, a1 = m10|m01, a2 = m20 - m00 | m11 |
-//    m02 - m00, a3 = m30 - 3 m10 | m21 - m01 | m12 - m10 | m03 - 3 m01 written
-//    into w_i sum_n a_(n) : H_(n)(c_i) / n!.
-//  herm[i][k]: the same reconstruction on the Hermite coefficients a_k:
+//  herm[i][k]: the N = 3 Grad reconstruction (Eq. gradGeneralTransform with rT_L =
+//    1) on the Hermite coefficients a_k (same ordering as the moments):
 //    pop_i = sum_k herm[i][k] a_k = w_i (a0 + a1.H1 + a2:H2/2 + a3:H3/6).
 struct VelocityTables {
-    double recon[kQ][kNM];
     double herm[kQ][kNM];
 };
 
@@ -54,15 +48,9 @@ constexpr VelocityTables make_velocity_tables() {
         const double Hxx = cx * cx - 1.0, Hyy = cy * cy - 1.0, Hxy = cx * cy;
         const double Hxxx = cx * cx * cx - 3.0 * cx, Hyyy = cy * cy * cy - 3.0 * cy;
         const double Hxxy = Hxx * cy, Hxyy = cx * Hyy;
-        const double r[kNM] = {1.0 - 0.5 * Hxx - 0.5 * Hyy, cx - 0.5 * Hxxx - 0.5 * Hxyy,
-                               cy - 0.5 * Hxxy - 0.5 * Hyyy, 0.5 * Hxx, Hxy, 0.5 * Hyy,
-                               Hxxx / 6.0, 0.5 * Hxxy, 0.5 * Hxyy, Hyyy / 6.0};
         const double h[kNM] = {1.0, cx, cy, 0.5 * Hxx, Hxy, 0.5 * Hyy,
                                Hxxx / 6.0, 0.5 * Hxxy, 0.5 * Hxyy, Hyyy / 6.0};
-        for (int k = 0; k < kNM; ++k) {
-            t.recon[i][k] = w * r[k];
-            t.herm[i][k] = w * h[k];
-        }
+        for (int k = 0; k < kNM; ++k) t.herm[i][k] = w * h[k];
     }
     return t;
 }
@@ -129,14 +117,11 @@ __host__ __device__ constexpr double binom_c(int n, int k) {
     return factorial_c(n) / (factorial_c(k) * factorial_c(n - k));
 }
 
-// Reconstruction tables of a lattice (the D2Q16 tables above, written for any
+// Reconstruction tables of a lattice (the D2Q16 table above, written for any
 // order): herm[i][k(a,b)] = w_i He_a(c_ix) He_b(c_iy) / (a! b!), so that
-// pop_i = sum_k herm[i][k] A_k for Hermite coefficients A_ab; recon[i][k(p,q)]
-// = sum_{a >= p, b >= q} herm[i][k(a,b)] he_a[p] he_b[q], the same
-// reconstruction on the normalised central moments m_pq.
+// pop_i = sum_k herm[i][k] A_k for Hermite coefficients A_ab.
 template <class L>
 struct LatticeTables {
-    double recon[L::Q][L::NM];
     double herm[L::Q][L::NM];
 };
 
@@ -150,29 +135,19 @@ constexpr LatticeTables<L> make_lattice_tables() {
             const int a = mom_px(k), b = mom_py(k);
             t.herm[i][k] = w * he_value(a, cx) * he_value(b, cy) / (factorial_c(a) * factorial_c(b));
         }
-        for (int k = 0; k < L::NM; ++k) {
-            const int p = mom_px(k), q = mom_py(k);
-            double r = 0.0;
-            for (int j = 0; j < L::NM; ++j) {
-                const int a = mom_px(j), b = mom_py(j);
-                if (a >= p && b >= q) r += t.herm[i][j] * he_coef(a, p) * he_coef(b, q);
-            }
-            t.recon[i][k] = r;
-        }
     }
     return t;
 }
 
 template <typename P, class L>
 struct LatticeTablesP {
-    P recon[L::Q][L::NM];
     P herm[L::Q][L::NM];
 };
 
 // ------------------------------------------------ mass-exact float tables
 // Rounding every table entry to the nearest float leaves the column that
-// carries the mass -- the weights w_i of a0 in the reconstruction, the weights
-// of m00 in the transformation -- summing to 1 only up to a few ulps (D2Q16:
+// carries the mass -- the weights w_i of a0 in the reconstruction -- summing to 1
+// only up to a few ulps (D2Q16:
 // the sixteen weights sum to 1 - 1.96e-8).  That deficit is the same at every
 // node and every step, so FP32 steps would lose (or gain) that fraction of
 // mass and energy each step: 4e-5 of the density over 2000 steps.  The column
@@ -248,14 +223,8 @@ constexpr LatticeTablesP<P, L> make_lattice_tables_p() {
     const LatticeTables<L> d = make_lattice_tables<L>();
     LatticeTablesP<P, L> t{};
     for (int i = 0; i < L::Q; ++i)
-        for (int k = 0; k < L::NM; ++k) {
-            t.recon[i][k] = P(d.recon[i][k]);
-            t.herm[i][k] = P(d.herm[i][k]);
-        }
-    if constexpr (sizeof(P) == 4) {
-        round_column_to_sum<L::Q1, L::NM>(d.recon, t.recon, 0, 1.0);
-        round_column_to_sum<L::Q1, L::NM>(d.herm, t.herm, 0, 1.0);
-    }
+        for (int k = 0; k < L::NM; ++k) t.herm[i][k] = P(d.herm[i][k]);
+    if constexpr (sizeof(P) == 4) round_column_to_sum<L::Q1, L::NM>(d.herm, t.herm, 0, 1.0);
     return t;
 }
 
@@ -323,7 +292,6 @@ __device__ __forceinline__ void hermite_from_central_n(const P m[L::NM], P A[L::
 
 template <typename P>
 struct VelocityTablesP {
-    P recon[kQ][kNM];
     P herm[kQ][kNM];
 };
 
@@ -332,25 +300,16 @@ constexpr VelocityTablesP<P> make_velocity_tables_p() {
     const VelocityTables d = make_velocity_tables();
     VelocityTablesP<P> t{};
     for (int i = 0; i < kQ; ++i)
-        for (int k = 0; k < kNM; ++k) {
-            t.recon[i][k] = P(d.recon[i][k]);
-            t.herm[i][k] = P(d.herm[i][k]);
-        }
-    if constexpr (sizeof(P) == 4) {  // mass-exact float tables (see above)
-        round_column_to_sum<4, kNM>(d.recon, t.recon, 0, 1.0);
+        for (int k = 0; k < kNM; ++k) t.herm[i][k] = P(d.herm[i][k]);
+    if constexpr (sizeof(P) == 4)  // a mass-exact float table (see above)
         round_column_to_sum<4, kNM>(d.herm, t.herm, 0, 1.0);
-    }
     return t;
 }
 
 static_assert(float_column_sum(make_velocity_tables_p<float>().herm, 0) == 1.0,
               "D2Q16 float weights must sum to 1 exactly");
-static_assert(float_column_sum(make_velocity_tables_p<float>().recon, 0) == 1.0,
-              "D2Q16 float m00 transform weights must sum to 1 exactly");
 static_assert(float_column_sum(make_lattice_tables_p<float, D2Q25>().herm, 0) == 1.0,
               "D2Q25 float weights must sum to 1 exactly");
-static_assert(float_column_sum(make_lattice_tables_p<float, D2Q25>().recon, 0) == 1.0,
-              "D2Q25 float m00 transform weights must sum to 1 exactly");
 
 // Central moments about d = (dx, dy), scaled by 1/s^(p+q): the normalised
 // moments m_pq of xi = (V - d)/s, from raw moments M about the same origin.
@@ -400,6 +359,10 @@ __device__ __forceinline__ void hermite_from_central(const P m[kNM], P a[kNM]) {
 // m = floor(y + 1/2) (quadratic).  Returns the first node.
 // y must be finite and within the int range (the step clamps the frame it
 // computes departure points from).
+template <int NP>
+__device__ __forceinline__ int stencil_base(double y) {
+    return int(NP == 4 ? floor(y) : floor(y + 0.5)) - 1;
+}
 template <int NP, typename P>
 __device__ __forceinline__ int lagrange(double y, P w[NP]) {
     if constexpr (NP == 4) {
@@ -433,12 +396,35 @@ __device__ __forceinline__ int lagrange(double y, P w[NP]) {
     }
 }
 
+// Index i wrapped (bc 0) or clamped into [0, n).  An index within one period of
+// the grid, the rule but for stencils longer than the grid, takes no division.
 __device__ __forceinline__ int wrap_index(int i, int n, int bc) {
     if (bc == 0) {
-        int r = i % n;
-        return r < 0 ? r + n : r;
+        int r = i < 0 ? i + n : (i >= n ? i - n : i);
+        if (unsigned(r) >= unsigned(n)) {
+            r = i % n;
+            r = r < 0 ? r + n : r;
+        }
+        return r;
     }
     return i < 0 ? 0 : (i >= n ? n - 1 : i);
+}
+
+// sqrt(T) and 1 / sqrt(T) of a frame temperature, from one reciprocal root (the
+// step and the moments pre-pass take the scale of a frame from here, so that
+// they form the same moments).
+__device__ __forceinline__ void frame_scale(double T, double &s, double &is) {
+    is = rsqrt(T);
+    s = T * is;
+}
+
+// The scale whose reciprocal is exactly the rounded is of a frame with sqrt(T) =
+// s: the gather reconstructs populations with 1 / sqrt(T) rounded to P, so their
+// moments follow with this scale (with s itself they would be off by the
+// rounding, 6e-8 in FP32, the same way in every step).
+template <typename P>
+__device__ __forceinline__ double rounded_scale(double s, P is) {
+    return sizeof(P) == 4 ? s * (2.0 - s * double(is)) : s;
 }
 
 }  // namespace pond

@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kBlock) void step_kernel(StepArgs a, DevState src,
         l2 = src.T[n];
     }
     GlobalTaps<P, NP, L> taps{mom, a.mstride, a.nx, a.ny, a.bc_x, a.bc_y, a.moff, a.wall_h, {}};
-    load_moments<P, nmom<L>()>(mom, a.mstride, a.moff + ref_node(x, y, a.nx), taps.ref);
+    taps.set_reference(x, y);
     node_step<P, NP, S, L>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
 }
 
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(TX *TY) POND_TILED_ATTR(P, S, TX *TY, L) void step_
                                                             DevState dst, P *__restrict__ mom_out,
                                                             DevCounters *cnt, int cap, int tiles_x) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ int red[4 * red_slots<TX * TY>()];
+    __shared__ int red[bound_slots<TX * TY>()];
     int tx, ty;
     band_tile<TX>(xcd_tile(blockIdx.x, gridDim.x), tiles_x, int(gridDim.x) / tiles_x, tx, ty);
     tile_step<P, NP, S, L>(a, src, mom, dst, mom_out, cnt, reinterpret_cast<P *>(smem_raw), cap,
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(kBlock) void ghost_check_kernel(StepArgs a, const d
         stencil_extent<NP, L>(y, uy[n], sqrt(fmax(T[n], 0.0)), lo, hi);
         out = lo < -a.wall_h || hi > a.ny - 1 + a.wall_h;
     }
-    const unsigned long long c = wave_sum((unsigned long long)out);
+    const unsigned long long c = wave_count(out);
     if ((threadIdx.x & 63) == 0 && c) atomicAdd(&cnt->ghost_overrun, c);
 }
 

@@ -24,11 +24,12 @@ using namespace pond;
 
 namespace {
 
-// Workspace size: 64 MiB.  With the counters at its start, it holds the two
-// sets of moment planes of up to ~419 000 nodes in FP32 on D2Q16 (80 B per
+// Workspace size: the counters, then 64 MiB less 256 bytes for the two sets of
+// moment planes of up to ~419 000 nodes in FP32 on D2Q16 (80 B per
 // node per set: e.g. 640 x 640), ~209 000 in FP64 (e.g. 456 x 456), ~262 000
 // in FP32 on D2Q25 (128 B per node per set: 512 x 512).
-constexpr size_t kWorkspaceBytes = size_t(64) << 20;
+constexpr size_t kPlaneBytes = (size_t(64) << 20) - kAlign;
+constexpr size_t kWorkspaceBytes = kPlaneBytes + (sizeof(DevCounters) + kAlign - 1) / kAlign * kAlign;
 
 static __device__ __align__(256) unsigned char scratch[kWorkspaceBytes];
 
@@ -55,7 +56,9 @@ pond_status workspace(void **out) {
 
 // Zeroes the counters with a kernel (no memset node if the caller captures).
 __global__ void clear_counters_kernel(DevCounters *c) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *c = DevCounters{};
+    static_assert(sizeof(DevCounters) % sizeof(unsigned long long) == 0, "cleared as 64-bit words");
+    unsigned long long *w = reinterpret_cast<unsigned long long *>(c);
+    for (size_t k = threadIdx.x; k < sizeof(DevCounters) / sizeof *w; k += blockDim.x) w[k] = 0;
 }
 
 bool device_pointer(const void *ptr) {
@@ -71,7 +74,7 @@ bool device_pointer(const void *ptr) {
 template <typename P>
 hipError_t run_steps(const StepArgs &a, const TileConfig &tc, DevState st[2], P *mom[2],
                      DevCounters *cnt, int64_t nsteps, hipStream_t s) {
-    hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, cnt);
+    hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(256), 0, s, cnt);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = launch_moments_prepass<P>(a, st[0], mom[0], s);
     if (e == hipSuccess && a.wall_h) e = launch_wall_ghosts<P>(a, st[0], mom[0], s);
@@ -100,12 +103,12 @@ pond_status pond_step_noalloc(const pond_params *p, const double *u_ref, void *f
     const size_t psize = dbl ? sizeof(double) : sizeof(float);
     const size_t mom_bytes =
         align_up(size_t(moment_plane_nodes(*p)) * moment_values(p->lattice, dbl) * psize);
-    const size_t need = align_up(sizeof(DevCounters)) + 2 * mom_bytes;
-    if (need > kWorkspaceBytes)
+    const size_t need = 2 * mom_bytes;
+    if (need > kPlaneBytes)
         return fail(POND_ERR_OUT_OF_MEMORY,
                     "%d x %d nodes need %zu bytes of workspace; pond_step_noalloc has %zu "
                     "(use pond_create / pond_step for larger grids)",
-                    p->nx, p->ny, need, kWorkspaceBytes);
+                    p->nx, p->ny, need, kPlaneBytes);
     void *ws = nullptr;
     if ((s = workspace(&ws)) != POND_OK) return s;
 
@@ -154,6 +157,7 @@ pond_status pond_step_noalloc(const pond_params *p, const double *u_ref, void *f
     e = hipMemcpyAsync(&h, cnt, sizeof h, hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return hip_fail(e, "pond_step_noalloc counters");
+    h.fold();
     stats->steps = nsteps;
     stats->node_updates = nsteps * N;
     stats->pc_iterations = int64_t(h.pc_iterations);

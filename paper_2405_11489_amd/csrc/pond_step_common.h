@@ -13,11 +13,6 @@
 
 #include <utility>
 
-// Stencil rows interpolated per loop trip in the HBM tap gather.
-#ifndef POND_ROW_UNROLL
-#define POND_ROW_UNROLL 1
-#endif
-
 #include "pond_device.h"
 #include "pond_internal.h"
 
@@ -173,31 +168,14 @@ constexpr unsigned lds_node_bytes() {
 }
 
 template <typename P, class L>
-__device__ __forceinline__ void load_node_lds(const P *lds, int idx, P *M) {
+__device__ __forceinline__ void load_node_lds(const P *lds, int idx, int cap, P *M) {
+    if constexpr (lds_planar<P, L>()) {
+        load_moments<P, nmom<L>()>(lds, cap, idx, M);
+        return;
+    }
     using MV = MomVec<P, nmom<L>()>;
     using V = typename MV::V;
     const V *b = reinterpret_cast<const V *>(lds) + idx * lds_stride<P, L>();
-#pragma unroll
-    for (int k = 0; k < MV::G; ++k) {
-        const V v = b[k];
-        if constexpr (MV::W == 4) {
-            M[4 * k] = v.x;
-            M[4 * k + 1] = v.y;
-            M[4 * k + 2] = v.z;
-            M[4 * k + 3] = v.w;
-        } else {
-            M[2 * k] = v.x;
-            M[2 * k + 1] = v.y;
-        }
-    }
-}
-
-// The same from the node's byte offset in the LDS array.
-template <typename P, class L>
-__device__ __forceinline__ void load_node_lds_at(const P *lds, unsigned off, P *M) {
-    using MV = MomVec<P, nmom<L>()>;
-    using V = typename MV::V;
-    const V *b = reinterpret_cast<const V *>(reinterpret_cast<const char *>(lds) + off);
 #pragma unroll
     for (int k = 0; k < MV::G; ++k) {
         const V v = b[k];
@@ -256,7 +234,7 @@ __device__ __forceinline__ const VelocityTablesP<double> &vtab<double>() {
     return kTabD;
 }
 
-// Reconstruction tables of lattice L (recon, herm; see pond_device.h).
+// Reconstruction table of lattice L (herm; see pond_device.h).
 template <typename P, class L>
 __device__ __forceinline__ const auto &ltab() {
     if constexpr (L::Q == 16)
@@ -267,48 +245,6 @@ __device__ __forceinline__ const auto &ltab() {
         return kTab25D;
 }
 
-// Lattice monomials c(a)^p c(b)^q of every velocity i = Q1 a + b (exponents
-// of moment k), for the lattice sums of the per-velocity gather.
-template <typename P, class L>
-struct LatticeMonomials {
-    P m[L::Q][L::NM];
-};
-template <typename P, class L>
-constexpr LatticeMonomials<P, L> make_lattice_monomials() {
-    LatticeMonomials<P, L> t{};
-    for (int i = 0; i < L::Q; ++i) {
-        const double ca = L::c(i / L::Q1), cb = L::c(i % L::Q1);
-        for (int k = 0; k < L::NM; ++k) {
-            double v = 1.0;
-            for (int p = 0; p < mom_px(k); ++p) v *= ca;
-            for (int q = 0; q < mom_py(k); ++q) v *= cb;
-            t.m[i][k] = P(v);
-        }
-    }
-    return t;
-}
-static __constant__ LatticeMonomials<float, D2Q16> kMono16F = make_lattice_monomials<float, D2Q16>();
-static __constant__ LatticeMonomials<double, D2Q16> kMono16D = make_lattice_monomials<double, D2Q16>();
-static __constant__ LatticeMonomials<float, D2Q25> kMono25F = make_lattice_monomials<float, D2Q25>();
-static __constant__ LatticeMonomials<double, D2Q25> kMono25D = make_lattice_monomials<double, D2Q25>();
-
-template <typename P, class L>
-__device__ __forceinline__ const LatticeMonomials<P, L> &lmono() {
-    if constexpr (L::Q == 16) {
-        if constexpr (sizeof(P) == 4)
-            return kMono16F;
-        else
-            return kMono16D;
-    } else if constexpr (sizeof(P) == 4) {
-        return kMono25F;
-    } else {
-        return kMono25D;
-    }
-}
-
-// Tap source reading the HBM moment planes with periodic / clamp wrapping.
-// gather() accumulates sum_{p,q} wx[p] wy[q] M(bx + p, by + q) for the NP x NP
-// stencil whose first node is (bx, by) in unwrapped grid coordinates.
 // Moment-plane row of the (unwrapped) grid row y: periodic wrap, clamp, or with
 // walls (bc 2) the ghost rows -wall_h .. -1 and ny .. ny + wall_h - 1 around
 // the grid (rows further out read the last ghost row).
@@ -317,8 +253,10 @@ __device__ __forceinline__ int mom_row(int y, int ny, int bc, int wall_h) {
     return wrap_index(y, ny, bc);
 }
 
+// Tap source reading the HBM moment planes with periodic / clamp wrapping.
+//
 // Reference blocks.  The gather interpolates the deviations M - M_ref of the
-// taps' moments from those of a reference node and starts its sums at M_ref:
+// taps' moments from those of a reference node and adds M_ref's share once:
 // equal to interpolating M itself (the weights sum to 1), but the rounding of
 // the weights -- whose sum differs from 1 by ~1e-8 in FP32, the same way at
 // every node of a uniform flow -- then scales only the deviation.  (Otherwise a
@@ -327,197 +265,102 @@ __device__ __forceinline__ int mom_row(int y, int ny, int bc, int wall_h) {
 // the aligned kRefBlockX x kRefBlockY block holding it: every tile shape
 // divides the block, so a tile has one reference, and every kernel and tile
 // shape interpolate the same deviations.
+//
+// FP64 interpolates the moments themselves (the weights' sum is 1 to 1e-16
+// there): where the taps' state lies far from the reference node's, the
+// populations of deviations would cancel against the reference's share, and
+// lose that factor in every step (the 400 x 1 shock tube, density 1 against
+// 0.125: 7e-12 off the oracle after 400 steps instead of 1e-13).
 constexpr int kRefBlockX = 256, kRefBlockY = 16;
+template <typename P>
+constexpr bool deviations() { return sizeof(P) == 4; }
 __device__ __forceinline__ long long ref_node(int x, int y, int nx) {
     return (long long)(y / kRefBlockY * kRefBlockY) * nx + (x / kRefBlockX * kRefBlockX);
 }
 
 template <typename P, int NP, class L = D2Q16>
 struct GlobalTaps {
+    using MV = MomVec<P, nmom<L>()>;
+    using V = typename MV::V;
     const P *mom;
     long long N;  // nodes per moment plane
     int nx, ny, bc_x, bc_y;
     long long moff;  // node offset of grid row 0
     int wall_h;
-    P ref[nmom_padded<P, L>()];  // moments of the reference node
+    P ref[deviations<P>() ? nmom_padded<P, L>() : 1];  // moments of the reference node
 
-    // the interpolation sums start at the reference moments
-    __device__ __forceinline__ void init(P Mf[L::NM], P Mg[L::NM]) const {
+    // reads the reference of destination node (x, y)
+    __device__ __forceinline__ void set_reference(int x, int y) {
+        if constexpr (deviations<P>())
+            load_moments<P, nmom<L>()>(mom, N, moff + ref_node(x, y, nx), ref);
+    }
+    __device__ __forceinline__ P ref_at(int k) const { return deviations<P>() ? ref[k] : P(0); }
+    // a single grid row without walls: every stencil row is row 0
+    __device__ __forceinline__ bool flat() const { return ny == 1 && bc_y != 2; }
+    __device__ __forceinline__ bool inside(int, int, int, int) const { return false; }
+
+    // the moments of the (unwrapped) grid node (x, y), as deviations from the
+    // reference node's
+    __device__ __forceinline__ void read(int x, int y, P *M) const {
+        const long long row = moff + (long long)mom_row(y, ny, bc_y, wall_h) * nx;
+        load_moments<P, nmom<L>()>(mom, N, row + wrap_index(x, nx, bc_x), M);
+        if constexpr (deviations<P>()) {
 #pragma unroll
-        for (int k = 0; k < L::NM; ++k) {
-            Mf[k] = ref[k];
-            Mg[k] = ref[L::NM + k];
+            for (int k = 0; k < nmom<L>(); ++k) M[k] -= ref[k];
         }
     }
-
-    __device__ __forceinline__ P ref_at(int k) const { return ref[k]; }
-
-    // Stencil rows r0 .. r0 + n - 1 (unwrapped) of the column stencil bx .. bx +
-    // NP - 1: for each row r, in ascending order, X = sum_p wx[p] (M(bx + p, r) -
-    // M_ref) over the 2 NM moments (the x-pass), handed to visit(r, seg, X).
-    template <class Visit>
-    __device__ __forceinline__ void rows(int bx, const P wx[NP], int r0, int n, int seg,
-                                         Visit &visit) const {
-        int col[NP];
-#pragma unroll
-        for (int j = 0; j < NP; ++j) col[j] = wrap_index(bx + j, nx, bc_x);
-#pragma unroll 1
-        for (int t = 0; t < n; ++t) {
-            const long long row = moff + (long long)mom_row(r0 + t, ny, bc_y, wall_h) * nx;
-            P X[2 * L::NM];
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                P M[nmom_padded<P, L>()];
-                load_moments<P, nmom<L>()>(mom, N, row + col[p], M);
-#pragma unroll
-                for (int k = 0; k < 2 * L::NM; ++k) {
-                    const P dv = M[k] - ref[k];
-                    X[k] = p == 0 ? wx[p] * dv : X[k] + wx[p] * dv;
-                }
-            }
-            visit(r0 + t, seg, X);
-        }
-    }
-
-    // adds sum_{p,q} wx[p] wy[q] (M(bx + p, by + q) - M_ref)
-    __device__ __forceinline__ void gather(int bx, int by, const P wx[NP], const P wy[NP],
-                                           P Mf[L::NM], P Mg[L::NM]) const {
-        int col[NP];
-#pragma unroll
-        for (int j = 0; j < NP; ++j) col[j] = wrap_index(bx + j, nx, bc_x);
-#pragma unroll POND_ROW_UNROLL
-        for (int q = 0; q < NP; ++q) {
-            const long long row = moff + (long long)mom_row(by + q, ny, bc_y, wall_h) * nx;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const P W = wx[p] * wy[q];
-                P M[nmom_padded<P, L>()];
-                load_moments<P, nmom<L>()>(mom, N, row + col[p], M);
-#pragma unroll
-                for (int k = 0; k < L::NM; ++k) {
-                    Mf[k] += W * (M[k] - ref[k]);
-                    Mg[k] += W * (M[L::NM + k] - ref[L::NM + k]);
-                }
-            }
-        }
-    }
+    // nothing is staged (never called: inside() is false)
+    struct Row {
+        __device__ __forceinline__ V operator()(int, int) const { return V{}; }
+        __device__ __forceinline__ void next() {}
+    };
+    __device__ __forceinline__ Row staged(int, int) const { return Row{}; }
 };
-
-__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 
 // Lanes of the wave for which c holds (a ballot and a scalar bit count).
 __device__ __forceinline__ unsigned long long wave_count(bool c) {
     return (unsigned long long)__popcll(__ballot(c));
 }
 
-// Coefficients B with pop_i = sum_j B_j M_j for raw moments M (about u_ref):
-// the reconstruction weights r of velocity i on the normalised central
-// moments about d = (dx, dy) (frame velocity - u_ref) with scale is = 1/sqrt(T),
-// composed with that shift and scaling (the transpose of central_normalised).
-// One coefficient vector serves both f and g.
-//
-// Each coefficient is the table weight plus the terms of the shift: the shift
-// terms are summed first and the weight added last, in one rounding.  Added
-// one by one onto the weight, each term would round at the weight's ulp, and
-// over the sixteen velocities the coefficients of m00 (the mass) would sum to
-// 1 + 7e-9 on average for frames within 1e-3 of u_ref -- a mass drift of that
-// size every step in FP32.  Summed first, the single rounding is unbiased.
-template <typename P>
-__device__ __forceinline__ void pop_coeffs(const P r[kNM], P dx, P dy, P is, P B[kNM]) {
-    const P is2 = is * is, is3 = is2 * is;
-    const P r00 = r[0], r10 = r[1] * is, r01 = r[2] * is;
-    const P r20 = r[3] * is2, r11 = r[4] * is2, r02 = r[5] * is2;
-    const P r30 = r[6] * is3, r21 = r[7] * is3, r12 = r[8] * is3, r03 = r[9] * is3;
-    const P ex = -dx, ey = -dy, exx = ex * ex, eyy = ey * ey, exy = ex * ey;
-    B[9] = r03;
-    B[8] = r12;
-    B[7] = r21;
-    B[6] = r30;
-    B[5] = r02 + (ex * r12 + P(3) * ey * r03);
-    B[4] = r11 + (P(2) * ex * r21 + P(2) * ey * r12);
-    B[3] = r20 + (P(3) * ex * r30 + ey * r21);
-    B[2] = r01 + (ex * r11 + P(2) * ey * r02 + exx * r21 + P(2) * exy * r12 + P(3) * eyy * r03);
-    B[1] = r10 + (P(2) * ex * r20 + ey * r11 + P(3) * exx * r30 + P(2) * exy * r21 + eyy * r12);
-    B[0] = r00 + (ex * r10 + ey * r01 + exx * r20 + exy * r11 + eyy * r02 + exx * ex * r30 +
-                  exx * ey * r21 + ex * eyy * r12 + eyy * ey * r03);
-}
-
-// pop_coeffs for any order: B_rt = sum_{p >= r, q >= t} r_pq is^(p+q) C(p,r) C(q,t)
-// (-dx)^(p-r) (-dy)^(q-t), the shift applied in y, then in x.
-template <class L, typename P>
-__device__ __forceinline__ void pop_coeffs_n(const P r[L::NM], P dx, P dy, P is, P B[L::NM]) {
-    constexpr int N = L::N;
-    P ex[N + 1], ey[N + 1], sc[N + 1];
-    ex[0] = ey[0] = sc[0] = P(1);
-#pragma unroll
-    for (int j = 1; j <= N; ++j) {
-        ex[j] = ex[j - 1] * (-dx);
-        ey[j] = ey[j - 1] * (-dy);
-        sc[j] = sc[j - 1] * is;
-    }
-    P R[L::NM], T[L::NM];
-#pragma unroll
-    for (int k = 0; k < L::NM; ++k) R[k] = r[k] * sc[mom_px(k) + mom_py(k)];
-    // each stage sums its shift terms first and adds the leading term last (see
-    // pop_coeffs)
-#pragma unroll
-    for (int k = 0; k < L::NM; ++k) {
-        const int p = mom_px(k), t = mom_py(k);
-        P acc = P(0);
-#pragma unroll
-        for (int q = t + 1; q <= N - p; ++q)
-            acc += P(binom_c(q, t)) * ey[q - t] * R[mom_index(p, q)];
-        T[k] = R[k] + acc;
-    }
-#pragma unroll
-    for (int k = 0; k < L::NM; ++k) {
-        const int rr = mom_px(k), t = mom_py(k);
-        P acc = P(0);
-#pragma unroll
-        for (int p = rr + 1; p <= N - t; ++p)
-            acc += P(binom_c(p, rr)) * ex[p - rr] * T[mom_index(p, t)];
-        B[k] = T[k] + acc;
-    }
-}
-
 // Moments sum_i f_i V_ix^p V_iy^q of Q populations at the velocities V_i =
 // s c_i + d (c_i = (c(a), c(b)) for i = Q1 a + b; one scale s and offset d for
 // all i) through the lattice sums C_pq = sum_i f_i c(a)^p c(b)^q, which the
-// x-components build in turn: column_add takes population (a, b) into S_q =
-// sum_b f_(a,b) c(b)^q, column_flush adds c(a)^p S_q to C_pq once the
-// x-component is done, and moments_from_lattice_sums expands (s c + d)^p by
-// the binomial theorem at the end.  (Q1 operations per population and NM per
-// x-component, where the monomials of each V_i and their products with f_i
-// cost about 3 NM.)
-template <class L, typename P>
-__device__ __forceinline__ void column_add(P S[L::N + 1], int b, P f) {
-    const P cb = P(L::c(b));
-    S[0] += f;
-    if (cb == P(0)) return;  // the zero abscissa of an odd lattice
-    P cq = cb;
+// x-components build in turn: column_add takes the populations f[0..Q1) of
+// x-component a into S_q = sum_b f_b c(b)^q (the even and odd parts of +-c(b)
+// first) and adds c(a)^p S_q to C_pq; moments_from_lattice_sums expands
+// (s c + d)^p by the binomial theorem at the end.  (Three operations per
+// population and NM per x-component, where the monomials of each V_i and their
+// products with f_i cost about 3 NM.)  Weighted: the populations come over
+// their weights w(a) w(b).
+template <class L, bool Weighted = false, typename P>
+__device__ __forceinline__ void column_add(P C[L::NM], const P f[L::Q1], int a) {
+    P S[L::N + 1];
 #pragma unroll
-    for (int q = 1; q <= L::N; ++q) {
-        S[q] += f * cq;
-        cq *= cb;
+    for (int h = 0; h < L::Q1 / 2; ++h) {
+        const double cb = L::c(L::Q1 - 1 - h);
+        const P even = f[L::Q1 - 1 - h] + f[h], odd = f[L::Q1 - 1 - h] - f[h];
+        double cq = Weighted ? L::w(h) : 1.0;
+#pragma unroll
+        for (int q = 0; q <= L::N; ++q) {
+            const P k = P(cq), v = q % 2 ? odd : even;
+            if (q == 0 && !Weighted)
+                S[0] = h == 0 ? v : S[0] + v;
+            else
+                S[q] = h == 0 ? k * v : S[q] + k * v;
+            cq *= cb;
+        }
     }
-}
-
-template <class L, typename P>
-__device__ __forceinline__ void column_flush(P C[L::NM], P S[L::N + 1], int a) {
+    if constexpr (L::Q1 % 2 == 1)  // the zero abscissa
+        S[0] += Weighted ? P(L::w(L::Q1 / 2)) * f[L::Q1 / 2] : f[L::Q1 / 2];
     const P ca = P(L::c(a));
-    P cp = P(1);
+    P cp = Weighted ? P(L::w(a)) : P(1);
 #pragma unroll
     for (int p = 0; p <= L::N; ++p) {
 #pragma unroll
-        for (int q = 0; p + q <= L::N; ++q) C[mom_index(p, q)] += p == 0 ? S[q] : cp * S[q];
+        for (int q = 0; p + q <= L::N; ++q)
+            C[mom_index(p, q)] += p == 0 && !Weighted ? S[q] : cp * S[q];
         cp *= ca;
     }
-#pragma unroll
-    for (int q = 0; q <= L::N; ++q) S[q] = P(0);
 }
 
 template <class L, typename P>
@@ -649,195 +492,11 @@ __device__ __forceinline__ void source_gradient(const StepArgs &a, const DevStat
     for (int k = 0; k < 4; ++k) g[k] = 2.0 * ga[k] - gb[k];
 }
 
-// FP32 D2Q25 shares its x-pass too (gather_shared_rows_transformed; 0: the
-// per-velocity gather).
-#ifndef POND_D2Q25_SHARED
-#define POND_D2Q25_SHARED 1
-#endif
+}  // namespace pond
 
-// Velocities per shared x-pass of the FP32 D2Q16 gather (4: the Q1 velocities
-// of one x-component; 2: half of them; 1: no sharing, every velocity gathers its
-// own NP x NP taps).  FP64 and D2Q25 gather per velocity.
-#ifndef POND_VEL_GROUP
-#define POND_VEL_GROUP 4
-#endif
-template <typename P, class L>
-constexpr int vel_group() {
-    return (L::Q == 16 && sizeof(P) == 4) ? POND_VEL_GROUP : 1;
-}
+#include "pond_gather.h"
 
-// The gather of every velocity of a D2Q16 node in the iterate frame (departure
-// offsets xu = x - u, yu = y - u relative to the node, scale sc = sqrt(T),
-// frame shift (dux, duy) from u_ref and 1 / sqrt(T) = is), with the
-// x-interpolation shared: the VG velocities of a group have the same x-component
-// c(ia), so the same departure abscissa and column stencil, and differ only in
-// their rows.  Each row of the union of their row stencils is interpolated along
-// x once (taps.rows); every velocity whose stencil holds the row takes that
-// x-pass with its row weight, through its frame-transformation coefficients
-// (the scalar f_i = B_i . I_i distributes over the rows).  When the union is
-// longer than the separate stencils (hot flows), each velocity's rows are
-// visited on their own; the sums are the same either way.  take(b, cx, cy,
-// f_i, g_i) receives each gathered population pair (i = Q1 ia + b), and
-// column(ia) follows the last of an x-component's.
-//
-// The populations handed over are those of the interpolated deviations from
-// the reference moments only: the reference's own share, B_i . M_ref, is the
-// same reconstruction of one moment vector for every velocity, and the
-// reconstruction keeps the moments up to order three (the quadrature is exact
-// to degree seven), so its share of every sum that take forms -- mass,
-// momentum, energy, the lab moments -- follows from M_ref itself; the caller
-// adds it once after the gather.  (The share then enters the sums exactly,
-// with no rounding of the coefficients B_i.)
-template <typename P, int NP, class L, int VG, class Taps, class Take, class Column>
-__device__ __forceinline__ void gather_shared_rows(const Taps &taps, const VelocityTablesP<P> &tab,
-                                                   double xu, double yu, double sc, P dux, P duy,
-                                                   P is, Take &take, Column &column) {
-    constexpr int NM = L::NM;
-    static_assert(L::Q1 % VG == 0, "velocity groups split the x-component's velocities");
-#pragma unroll 1
-    for (int ia = 0; ia < L::Q1; ++ia) {
-        const double cx = L::c(ia);
-        P wx[NP];
-        const int bx = lagrange<NP>(fma(-sc, cx, xu), wx);
-#pragma unroll 1
-        for (int g = 0; g < L::Q1 / VG; ++g) {
-            // rows and weights of the group's velocities b = g VG + v: their
-            // departure ordinates y - u - sqrt(T) c(b) descend with b, and so do
-            // their first stencil rows by[v]
-            int by[VG];
-            P wq[VG][NP];  // row weights, consumed first to last
-            P B[VG][NM];
-            P af[VG], ag[VG];
-#pragma unroll
-            for (int v = 0; v < VG; ++v) {
-                const int b = g * VG + v;
-                by[v] = lagrange<NP>(fma(-sc, L::c(b), yu), wq[v]);
-                pop_coeffs(tab.recon[L::Q1 * ia + b], dux, duy, is, B[v]);
-                af[v] = ag[v] = P(0);
-            }
-            auto visit = [&](int r, int seg, const P (&X)[2 * NM]) {
-#pragma unroll
-                for (int v = 0; v < VG; ++v) {
-                    const bool mine = seg < 0 ? unsigned(r - by[v]) < unsigned(NP) : seg == v;
-                    if (mine) {
-                        const P w = wq[v][0];
-#pragma unroll
-                        for (int q = 0; q + 1 < NP; ++q) wq[v][q] = wq[v][q + 1];
-                        P df = P(0), dg = P(0);
-#pragma unroll
-                        for (int k = 0; k < NM; ++k) {
-                            df += B[v][k] * X[k];
-                            dg += B[v][k] * X[NM + k];
-                        }
-                        af[v] += w * df;
-                        ag[v] += w * dg;
-                    }
-                }
-            };
-            const int span = by[0] - by[VG - 1] + NP;
-            if (span <= VG * NP) {
-                taps.rows(bx, wx, by[VG - 1], span, -1, visit);
-            } else {
-#pragma unroll 1
-                for (int v = 0; v < VG; ++v) {
-                    int r0 = by[0];
-#pragma unroll
-                    for (int u = 1; u < VG; ++u) r0 = v == u ? by[u] : r0;
-                    taps.rows(bx, wx, r0, NP, v, visit);
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < VG; ++v) {
-                const int b = g * VG + v;
-                take(b, cx, L::c(b), af[v], ag[v]);
-            }
-        }
-        column(ia);
-    }
-}
-
-// D2Q25 in FP32 shares the x-pass between the five velocities of an
-// x-component too, in a form that holds no per-velocity coefficients (their 75
-// registers do not fit beside the 30-moment rows): each row of the union of the
-// row stencils is interpolated along x once and turned into the normalised
-// central moments of the iterate frame once (central_normalised_n: a linear
-// map, so it commutes with the row weights), and each velocity whose stencil
-// holds the row adds its row weight times the reconstruction weights (the
-// lattice tables, uniform across lanes) dotted with those moments.  As in
-// gather_shared_rows, the populations handed over are those of the deviations
-// from the reference moments; the order-4 reconstruction keeps the moments up
-// to order four (D1Q5 integrates exactly to degree nine), so the reference's
-// share of the sums is added by the caller, once.
-template <typename P, class L>
-constexpr bool shared_rows_transformed() {
-    return L::Q == 25 && sizeof(P) == 4 && POND_D2Q25_SHARED != 0;
-}
-
-template <typename P, int NP, class L, class Taps, class Tab, class Take, class Column>
-__device__ __forceinline__ void gather_shared_rows_transformed(const Taps &taps, const Tab &tab,
-                                                               double xu, double yu, double sc,
-                                                               P dux, P duy, P is, Take &take,
-                                                               Column &column) {
-    constexpr int NM = L::NM, Q1 = L::Q1;
-#pragma unroll 1
-    for (int ia = 0; ia < Q1; ++ia) {
-        const double cx = L::c(ia);
-        P wx[NP];
-        const int bx = lagrange<NP>(fma(-sc, cx, xu), wx);
-        int by[Q1];
-        P wq[Q1][NP];  // row weights, consumed first to last
-        P af[Q1], ag[Q1];
-#pragma unroll
-        for (int b = 0; b < Q1; ++b) {
-            by[b] = lagrange<NP>(fma(-sc, L::c(b), yu), wq[b]);
-            af[b] = ag[b] = P(0);
-        }
-        auto visit = [&](int row, int seg, const P (&X)[2 * NM]) {
-            P Zf[NM], Zg[NM];
-            central_normalised_n<L>(X, dux, duy, is, Zf);
-            central_normalised_n<L>(X + NM, dux, duy, is, Zg);
-#pragma unroll
-            for (int b = 0; b < Q1; ++b) {
-                const bool mine = seg < 0 ? unsigned(row - by[b]) < unsigned(NP) : seg == b;
-                if (mine) {
-                    const P w = wq[b][0];
-#pragma unroll
-                    for (int q = 0; q + 1 < NP; ++q) wq[b][q] = wq[b][q + 1];
-                    // the velocity's weights are read from the constant table at
-                    // each visit (a scalar load): the x-component's 75 weights held
-                    // across the row loop would not fit the scalar registers and
-                    // would be spilled into vector-register lanes
-                    int row_tab = Q1 * ia + b;
-                    asm volatile("" : "+s"(row_tab));
-                    const P *r = tab.recon[row_tab];
-                    P df = P(0), dg = P(0);
-#pragma unroll
-                    for (int k = 0; k < NM; ++k) {
-                        df += r[k] * Zf[k];
-                        dg += r[k] * Zg[k];
-                    }
-                    af[b] += w * df;
-                    ag[b] += w * dg;
-                }
-            }
-        };
-        const int span = by[0] - by[Q1 - 1] + NP;
-        if (span <= Q1 * NP) {
-            taps.rows(bx, wx, by[Q1 - 1], span, -1, visit);
-        } else {
-#pragma unroll 1
-            for (int b = 0; b < Q1; ++b) {
-                int r0 = by[0];
-#pragma unroll
-                for (int u = 1; u < Q1; ++u) r0 = b == u ? by[u] : r0;
-                taps.rows(bx, wx, r0, NP, b, visit);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < Q1; ++b) take(b, cx, L::c(b), af[b], ag[b]);
-        column(ia);
-    }
-}
+namespace pond {
 
 // The whole step of one destination node (x, y) = node n whose time-t frame
 // is (l0, l1, l2), for the energy split S (0: total energy, 1: internal
@@ -848,12 +507,11 @@ __device__ __forceinline__ void gather_shared_rows_transformed(const Taps &taps,
 // moments pre-pass computes them.  Lanes with live == false take part in the
 // wave-level predictor-corrector exit and the counter reduction only.
 //
-// Per predictor-corrector gather, for each velocity i: departure point and
-// Lagrange weights, interpolation of the 2 NM moments, frame transformation of
-// the interpolated moments into the iterate frame (population i of f and g);
-// the FP64 sums rho, j, E and the lattice sums of the gathered populations
-// (their lab moments follow once, from the last gather's) are accumulated on
-// the fly, so no population array is kept.
+// Per predictor-corrector gather (gather_rows): the populations of f and g at
+// their departure points in the iterate frame, one x-component at a time; the
+// FP64 sums rho, j, E and the lattice sums of the gathered populations (their
+// lab moments follow once, from the last gather's) are accumulated on the fly,
+// so no population array is kept.
 template <typename P, int NP, int S, class L, class Taps>
 __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, int x, int y,
                                           long long n, bool live, double l0, double l1, double l2,
@@ -885,12 +543,12 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
     }
 
     // lab moments of a gather's populations from its lattice sums (frame scale sP,
-    // offset (dux, duy) from u_ref); the shared gathers sum the deviations from
-    // the reference moments, whose share is added here
+    // offset (dux, duy) from u_ref); where the gather sums the deviations from the
+    // reference moments, their share is added here
     auto lab_moments = [&](P sP, P dux, P duy) {
         moments_from_lattice_sums<L>(Cf, sP, dux, duy, Mf);
         moments_from_lattice_sums<L>(Cg, sP, dux, duy, Mg);
-        if constexpr (vel_group<P, L>() > 1 || shared_rows_transformed<P, L>()) {
+        if constexpr (deviations<P>()) {
 #pragma unroll
             for (int k = 0; k < NM; ++k) {
                 Mf[k] += taps.ref_at(k);
@@ -902,61 +560,59 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
     for (int it = 0; it < a.pc_max_iter; ++it) {
         itc += wave_count(!done);
         if (!done) {
-            const double s = sqrt(lg2);
+            double s, isd;
+            frame_scale(lg2, s, isd);
             if (a.bc_y == 2) {
                 // walls: every stencil row must lie within the ghost rows
                 int lo, hi;
                 stencil_extent<NP, L>(y, lg1, s, lo, hi);
                 if (lo < -a.wall_h || hi > a.ny - 1 + a.wall_h) overrun = true;
             }
-            const P sP = P(s), dux = P(lg0 - a.uref_x), duy = P(lg1 - a.uref_y), is = P(1.0 / s);
+            const P dux = P(lg0 - a.uref_x), duy = P(lg1 - a.uref_y), is = P(isd);
+            const double sr = rounded_scale(s, is);
+            const P sP = P(sr);
             // departure coordinates x - (s c + u) = (x - u) - s c, from the iterate
             // frame clamped to a finite range (a non-physical iterate, which the
             // test below flags, must still index inside the grid)
             const double sc = fmin(fmax(s, 0.0), 1.0e6);
             const double xu = double(x) - fmin(fmax(lg0, -1.0e8), 1.0e8);
             const double yu = double(y) - fmin(fmax(lg1, -1.0e8), 1.0e8);
-            double r = 0.0, jx = 0.0, jy = 0.0, E = 0.0, Eg = 0.0;
-            P Sf[L::N + 1], Sg[L::N + 1];
+            double r = 0.0, mx = 0.0, my = 0.0, m2 = 0.0, Eg = 0.0;
 #pragma unroll
             for (int k = 0; k < NM; ++k) Cf[k] = Cg[k] = P(0);
+            // x-component ia's populations gathered in the iterate frame, over their
+            // weights: the FP64 sums of f, f c and g (and f |c|^2), and the lattice sums
+            auto column = [&](int ia, const P (&f)[L::Q1], const P (&g)[L::Q1]) {
+                const double ca = L::c(ia), wa = gather_weight<P, L>(ia);
+                double s0 = 0.0, s1 = 0.0, s2 = 0.0, sg = 0.0;
 #pragma unroll
-            for (int q = 0; q <= L::N; ++q) Sf[q] = Sg[q] = P(0);
-            // population i = Q1 ia + b of f and g gathered in the iterate frame: the
-            // FP64 sums rho, j, E (sums) and the lattice sums of the gathered
-            // populations (take: through the column sums)
-            auto sums = [&](double cx, double cy, P fi, P gi) {
-                // conserved moments in FP64
-                const double fd = double(fi);
-                r += fd;
-                jx += fd * (s * cx + lg0);
-                jy += fd * (s * cy + lg1);
-                E += double(gi);
-                if constexpr (S == 2) {
-                    // non-translational split: f carries the translational energy
-                    Eg += double(gi);
-                    const double Cx = s * cx + lg0, Cy = s * cy + lg1;
-                    E += 0.5 * fd * (Cx * Cx + Cy * Cy);
+                for (int b = 0; b < L::Q1; ++b) {
+                    const double fd = double(f[b]), cb = L::c(b);
+                    const double wb = gather_weight<P, L>(b);
+                    s0 += wb * fd;
+                    if (cb != 0.0) s1 += (wb * cb) * fd;
+                    if constexpr (S == 2) s2 += (wb * cb * cb) * fd;
+                    sg += wb * double(g[b]);
                 }
+                s0 *= wa;
+                r += s0;
+                mx += ca * s0;
+                my += wa * s1;
+                if constexpr (S == 2) m2 += ca * ca * s0 + wa * s2;
+                Eg += wa * sg;
+                column_add<L, true>(Cf, f, ia);
+                column_add<L, true>(Cg, g, ia);
             };
-            auto take = [&](int b, double cx, double cy, P fi, P gi) {
-                sums(cx, cy, fi, gi);
-                column_add<L>(Sf, b, fi);
-                column_add<L>(Sg, b, gi);
-            };
-            auto column = [&](int ia) {
-                column_flush<L>(Cf, Sf, ia);
-                column_flush<L>(Cg, Sg, ia);
-            };
-            if constexpr (vel_group<P, L>() > 1 || shared_rows_transformed<P, L>()) {
-                if constexpr (vel_group<P, L>() > 1)
-                    gather_shared_rows<P, NP, L, vel_group<P, L>()>(taps, tab, xu, yu, sc, dux,
-                                                                     duy, is, take, column);
-                else
-                    gather_shared_rows_transformed<P, NP, L>(taps, tab, xu, yu, sc, dux, duy, is,
-                                                             take, column);
-                // the reference moments' share of the sums (moments about u_ref;
-                // the lab velocity is V + u_ref), added once after the deviations'
+            gather_rows<P, NP, L>(taps, xu, yu, sc, dux, duy, is, P(sr * sr), column);
+            // momentum, and in the non-translational split the energy f carries, at
+            // the velocities C = s c + u of the iterate frame
+            double jx = sr * mx + lg0 * r, jy = sr * my + lg1 * r, E = Eg;
+            if constexpr (S == 2)
+                E += 0.5 * (sr * sr * m2 + 2.0 * sr * (lg0 * mx + lg1 * my) +
+                            (lg0 * lg0 + lg1 * lg1) * r);
+            if constexpr (deviations<P>()) {
+                // the reference moments' share of the sums (moments about u_ref; the lab
+                // velocity is V + u_ref), added once after the deviations'
                 const double m00 = double(taps.ref_at(0));
                 const double m10 = double(taps.ref_at(mom_index(1, 0)));
                 const double m01 = double(taps.ref_at(mom_index(0, 1)));
@@ -971,53 +627,13 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
                     E += 0.5 * (m20 + m02) + a.uref_x * m10 + a.uref_y * m01 +
                          0.5 * (a.uref_x * a.uref_x + a.uref_y * a.uref_y) * m00;
                 }
-            } else {
-                // velocity i = Q1 ia + ib has x-component c(ia) and y-component c(ib):
-                // the x-stencil serves the Q1 velocities of one ia
-#pragma unroll 1
-                for (int ia = 0; ia < L::Q1; ++ia) {
-                    const double cx = L::c(ia);
-                    // departure point x - C_i(lam_bar) dt and its stencil, x then y
-                    P wx[NP];
-                    const int bx = lagrange<NP>(fma(-sc, cx, xu), wx);
-#pragma unroll 1
-                    for (int ib = 0; ib < L::Q1; ++ib) {
-                        const int i = L::Q1 * ia + ib;
-                        const double cy = L::c(ib);
-                        P wy[NP];
-                        const int by = lagrange<NP>(fma(-sc, cy, yu), wy);
-                        P If[NM], Ig[NM];
-                        taps.init(If, Ig);
-                        taps.gather(bx, by, wx, wy, If, Ig);
-                        // frame transformation of the interpolated moments: population i
-                        P B[NM];
-                        if constexpr (L::Q == 16)
-                            pop_coeffs(tab.recon[i], dux, duy, is, B);
-                        else
-                            pop_coeffs_n<L>(tab.recon[i], dux, duy, is, B);
-                        P fi = P(0), gi = P(0);
-#pragma unroll
-                        for (int k = 0; k < NM; ++k) {
-                            fi += B[k] * If[k];
-                            gi += B[k] * Ig[k];
-                        }
-                        // lattice sums with the velocity's monomials from the
-                        // table: column sums held across this loop would take
-                        // registers the FP64 kernels do not have
-                        sums(cx, cy, fi, gi);
-                        const P *mi = lmono<P, L>().m[i];
-#pragma unroll
-                        for (int k = 0; k < NM; ++k) {
-                            Cf[k] += fi * mi[k];
-                            Cg[k] += gi * mi[k];
-                        }
-                    }
-                }
             }
             rho = r;
             gsum = S == 2 ? Eg : E;
-            ln0 = jx / r;
-            ln1 = jy / r;
+            const double rinv = 1.0 / r;
+            ln0 = jx * rinv;
+            ln1 = jy * rinv;
+
             // total split: sum g = E = rho c_v T + |j|^2 / (2 rho); internal: sum g = rho c_v T;
             // non-translational: E = sum g + sum f |C|^2 / 2 = rho c_v T + |j|^2 / (2 rho)
             if constexpr (S == 1) lab_moments(sP, dux, duy);
@@ -1038,21 +654,22 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
                 ln2 = (E - 0.5 * (1.0 - 0.5 * a.omega) * PdU) /
                       (r * (a.cv + 0.25 * a.omega * (double(gxx) + double(gyy))));
             } else
-                ln2 = (E - (jx * jx + jy * jy) / (2.0 * r)) / (r * a.cv);
+                ln2 = (E - 0.5 * (jx * ln0 + jy * ln1)) * (rinv * a.rcv);
             if (!(r > 0.0) || !(ln2 > 0.0) || !isfinite(ln0) || !isfinite(ln1) || !isfinite(ln2) ||
                 !isfinite(E)) {
                 bad = true;
                 done = true;
             } else {
-                const double du = fmax(fabs(ln0 - lg0), fabs(ln1 - lg1)) / sqrt(ln2);
+                // du / sqrt(T) <= tol and dT / Tscale <= tol, without the divisions
+                const double du = fmax(fabs(ln0 - lg0), fabs(ln1 - lg1));
                 // FP64: the change of T relative to T.  FP32: relative to the scale of
                 // the energy T is recovered from, E / (rho c_v) (T itself in the internal
                 // split, T + |u|^2 / (2 c_v) in the total split): single-precision
                 // populations resolve E, and so T, only to a fraction of that scale
                 double Tscale = ln2;
-                if constexpr (sizeof(P) == 4) Tscale = E / (r * a.cv);
-                const double dT = fabs(ln2 - lg2) / Tscale;
-                if (fmax(du, dT) <= a.pc_tol) {
+                if constexpr (sizeof(P) == 4) Tscale = E * (rinv * a.rcv);
+                const double dT = fabs(ln2 - lg2);
+                if (du * du <= a.pc_tol * a.pc_tol * ln2 && dT <= a.pc_tol * Tscale) {
                     conv = true;
                     done = true;
                 } else if (it + 1 < a.pc_max_iter) {
@@ -1068,12 +685,14 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
     if (live) {
         if constexpr (S != 1) {
             // the last gather's frame (lam is only advanced when another gather follows)
-            const double s = sqrt(lg2);
-            lab_moments(P(s), P(lg0 - a.uref_x), P(lg1 - a.uref_y));
+            double s, isd;
+            frame_scale(lg2, s, isd);
+            lab_moments(P(rounded_scale(s, P(isd))), P(lg0 - a.uref_x), P(lg1 - a.uref_y));
         }
         // re-projection onto lam* = (ln0, ln1, ln2): Grad coefficients there
-        const double sT = sqrt(ln2);
-        const P is = P(1.0 / sT);
+        double sT, isT;
+        frame_scale(ln2, sT, isT);
+        const P is = P(isT);
         const P tx = P(ln0 - a.uref_x), ty = P(ln1 - a.uref_y);
         P m[NM], af[NM], ag[NM];
         // the zeroth moments are the exact FP64 sums of the gathered populations,
@@ -1138,8 +757,8 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
             double gqe[NM];
 #pragma unroll
             for (int k = 0; k < NM; ++k) gqe[k] = geq[k];
-            gqe[1] += dqx / sT;
-            gqe[2] += dqy / sT;
+            gqe[1] += dqx * isT;
+            gqe[2] += dqy * isT;
             const double om1 = a.omega1;
 #pragma unroll
             for (int k = 0; k < NM; ++k)
@@ -1166,23 +785,24 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
         const P decay = P(1.0 - om);
 #pragma unroll
         for (int k = 1; k < NM; ++k) af[k] *= decay;
+        // a non-physical node's populations are all NaN
+        if (bad) af[0] = ag[0] = P(NAN);
 
         // reconstruct and store the post-collision populations, and accumulate the
         // moments of the stored values about u_ref (the next step's taps)
         const P sTP = P(sT), u0 = P(ln0), u1 = P(ln1);
         const double Tst = bad ? NAN : ln2, uxst = bad ? NAN : ln0, uyst = bad ? NAN : ln1;
-        const P sM = P(sqrt(Tst)), dxM = P(uxst - a.uref_x), dyM = P(uyst - a.uref_y);
+        const P sM = P(bad ? NAN : sT), dxM = P(uxst - a.uref_x), dyM = P(uyst - a.uref_y);
         P MM[nmom_padded<P, L>()];
 #pragma unroll
         for (int k = 0; k < nmom_padded<P, L>(); ++k) MM[k] = P(0);
-        P Nf[NM], Ng[NM], Sf[L::N + 1], Sg[L::N + 1];  // lattice sums (column_add)
+        P Nf[NM], Ng[NM];  // lattice sums (column_add)
 #pragma unroll
         for (int k = 0; k < NM; ++k) Nf[k] = Ng[k] = P(0);
-#pragma unroll
-        for (int q = 0; q <= L::N; ++q) Sf[q] = Sg[q] = P(0);
         double mass = 0.0, gzero = 0.0;  // zeroth moments summed in FP64 (see above)
 #pragma unroll 1
         for (int ia = 0; ia < L::Q1; ++ia) {
+            P fc[L::Q1], gc[L::Q1];
 #pragma unroll
             for (int b = 0; b < L::Q1; ++b) {
                 const int i = L::Q1 * ia + b;
@@ -1200,16 +820,15 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
                     const P Cx = ex + u0, Cy = ey + u1;
                     gv -= src_w * ft * (ex * (ax + Cx * gxx + Cy * gyx) + ey * (ay + Cx * gxy + Cy * gyy));
                 }
-                if (bad) fv = gv = P(NAN);
                 out_store<kStreamPops>(&pop_plane<P>(dst.f, i, a.N)[n], fv);
                 out_store<kStreamPops>(&pop_plane<P>(dst.g, i, a.N)[n], gv);
-                column_add<L>(Sf, b, fv);
-                column_add<L>(Sg, b, gv);
+                fc[b] = fv;
+                gc[b] = gv;
                 mass += double(fv);
                 gzero += double(gv);
             }
-            column_flush<L>(Nf, Sf, ia);
-            column_flush<L>(Ng, Sg, ia);
+            column_add<L>(Nf, fc, ia);
+            column_add<L>(Ng, gc, ia);
         }
         moments_from_lattice_sums<L>(Nf, sM, dxM, dyM, MM);
         moments_from_lattice_sums<L>(Ng, sM, dxM, dyM, MM + NM);
@@ -1232,10 +851,11 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
     const unsigned long long nb = wave_count(live && bad);
     const unsigned long long no = wave_count(live && overrun);
     if ((threadIdx.x & 63) == 0) {
-        if (itc) atomicAdd(&cnt->pc_iterations, itc);
-        if (nc) atomicAdd(&cnt->nonconverged, nc);
-        if (nb) atomicAdd(&cnt->nonphysical, nb);
-        if (no) atomicAdd(&cnt->ghost_overrun, no);
+        DevCounters::Slot *slot = &cnt->slot[blockIdx.x % kCounterSlots];
+        if (itc) atomicAdd(&slot->pc_iterations, itc);
+        if (nc) atomicAdd(&slot->nonconverged, nc);
+        if (nb) atomicAdd(&slot->nonphysical, nb);
+        if (no) atomicAdd(&slot->ghost_overrun, no);
     }
 }
 

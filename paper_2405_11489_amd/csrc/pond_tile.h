@@ -6,215 +6,129 @@
 
 #include "pond_step_common.h"
 
-// Taps of a stencil row whose LDS loads are issued together; the row's later
-// taps are loaded only after these are consumed (0: the whole row at once).
-// Fewer loads in flight per lane -> fewer live registers -> more waves per
-// SIMD: FP32 165 VGPRs (3 waves) with groups of 2, FP64 238 (2 waves) with 1.
-// The four-wave FP32 kernel (512-lane blocks) loads one tap at a time: its
-// 128 VGPRs then spill 17 registers instead of 30.
-#ifndef POND_TAP_GROUP_F32
-#define POND_TAP_GROUP_F32 2
+#ifndef POND_WAVES_F32
+#define POND_WAVES_F32 2
 #endif
-#ifndef POND_TAP_GROUP_F64
-#define POND_TAP_GROUP_F64 1
+#ifndef POND_WAVES_F32_25
+#define POND_WAVES_F32_25 2
 #endif
-
-#ifndef POND_D2Q25_SHARED_WAVES
-#define POND_D2Q25_SHARED_WAVES 2
+#ifndef POND_WAVES_F64
+#define POND_WAVES_F64 1
+#endif
+#ifndef POND_WAVES_F64_25
+#define POND_WAVES_F64_25 1
 #endif
 
 namespace pond {
 
 // Tap source of a tile: the moments of the block's source region (unwrapped
-// rectangle [X0, X1] x [Y0, Y1], W wide, row-major) staged in LDS node-major
-// (lds_stride), cap nodes at most; a velocity whose stencil leaves the region
-// reads HBM.  With a
-// single grid row (flat_y) every stencil row is row 0, so the region is one
-// row and all NP stencil rows read it (same arithmetic as the HBM gather).
-// G: taps per group of LDS loads (the arithmetic does not depend on it).
-template <typename P, int NP, class L = D2Q16,
-          int G = sizeof(P) == 8 ? POND_TAP_GROUP_F64 : POND_TAP_GROUP_F32>
+// rectangle [X0, X1] x [Y0, Y1], W wide, row-major) staged in LDS (in FP32 as
+// deviations from the tile's reference node, rounded as GlobalTaps rounds them:
+// both give the same bits), cap nodes at most; rows whose stencil leaves the region read
+// HBM.  With a single grid row the region is that row.
+template <typename P, int NP, class L = D2Q16>
 struct TileTaps {
+    using MV = MomVec<P, nmom<L>()>;
+    using V = typename MV::V;
     const P *lds;
     int cap, X0, Y0, X1, Y1, W;
-    bool flat_y;
     GlobalTaps<P, NP, L> glob;
 
-    __device__ __forceinline__ void init(P Mf[L::NM], P Mg[L::NM]) const { glob.init(Mf, Mg); }
     __device__ __forceinline__ P ref_at(int k) const { return glob.ref[k]; }
-
-    // The x-pass over stencil rows r0 .. r0 + n - 1 (see GlobalTaps::rows): from
-    // LDS when the rows' stencil lies in the staged region, else from HBM (the
-    // staged moments are the deviations from the reference node, rounded as
-    // GlobalTaps rounds them, so both give the same bits).
-    template <class Visit>
-    __device__ __forceinline__ void rows(int bx, const P wx[NP], int r0, int n, int seg,
-                                         Visit &visit) const {
-        const bool inside =
-            bx >= X0 && bx + NP - 1 <= X1 && (flat_y || (r0 >= Y0 && r0 + n - 1 <= Y1));
-        if (inside && lds_planar<P, L>()) {
-            // grouped planes: group k of node idx at vector k * cap + idx, so the NP
-            // taps of a row are consecutive vectors of each group plane
-            using MV = MomVec<P, nmom<L>()>;
-            using V = typename MV::V;
-            const int rs = flat_y ? 0 : W;
-            int idx = (flat_y ? 0 : r0 - Y0) * W + (bx - X0);
-#pragma unroll 1
-            for (int t = 0; t < n; ++t) {
-                const V *b = reinterpret_cast<const V *>(lds) + idx;
-                P X[2 * L::NM];
-#pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    if (G > 0 && p > 0 && p % G == 0) asm volatile("" ::: "memory");
-                    P M[nmom_padded<P, L>()];
-#pragma unroll
-                    for (int k = 0; k < MV::G; ++k) {
-                        const V v = b[k * cap + p];
-                        if constexpr (MV::W == 4) {
-                            M[4 * k] = v.x;
-                            M[4 * k + 1] = v.y;
-                            M[4 * k + 2] = v.z;
-                            M[4 * k + 3] = v.w;
-                        } else {
-                            M[2 * k] = v.x;
-                            M[2 * k + 1] = v.y;
-                        }
-                    }
-#pragma unroll
-                    for (int k = 0; k < 2 * L::NM; ++k)
-                        X[k] = p == 0 ? wx[p] * M[k] : X[k] + wx[p] * M[k];
-                }
-                visit(r0 + t, seg, X);
-                idx += rs;
-            }
-        } else if (inside) {
-            constexpr unsigned NB = lds_node_bytes<P, L>();
-            const unsigned rowb = flat_y ? 0u : unsigned(W) * NB;
-            unsigned off = __umul24(unsigned(flat_y ? 0 : r0 - Y0), rowb) +
-                           __umul24(unsigned(bx - X0), NB);
-#pragma unroll 1
-            for (int t = 0; t < n; ++t) {
-                P X[2 * L::NM];
-#pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    if (G > 0 && p > 0 && p % G == 0) asm volatile("" ::: "memory");
-                    P M[nmom_padded<P, L>()];
-                    load_node_lds_at<P, L>(lds, off + unsigned(p) * NB, M);
-#pragma unroll
-                    for (int k = 0; k < 2 * L::NM; ++k)
-                        X[k] = p == 0 ? wx[p] * M[k] : X[k] + wx[p] * M[k];
-                }
-                visit(r0 + t, seg, X);
-                off += rowb;
-            }
-        } else {
-            int bxv = bx;
-            asm volatile("" : "+v"(bxv));
-            glob.rows(bxv, wx, r0, n, seg, visit);
-        }
+    __device__ __forceinline__ bool flat() const { return glob.flat(); }
+    // columns bx .. bx + m - 1 of rows r .. r + n - 1 are staged
+    __device__ __forceinline__ bool inside(int bx, int m, int r, int n) const {
+        return bx >= X0 && bx + m - 1 <= X1 && (flat() || (r >= Y0 && r + n - 1 <= Y1));
     }
 
-    // the staged moments are the deviations from the tile's reference node
-    __device__ __forceinline__ void gather(int bx, int by, const P wx[NP], const P wy[NP],
-                                           P Mf[L::NM], P Mg[L::NM]) const {
-        const bool inside =
-            bx >= X0 && bx + NP - 1 <= X1 && (flat_y || (by >= Y0 && by + NP - 1 <= Y1));
-        if (inside && lds_planar<P, L>()) {
-            // grouped planes (node idx, group k at vector k * cap + idx)
-            const int rs = flat_y ? 0 : W;
-            const int base = (flat_y ? 0 : by - Y0) * W + (bx - X0);
-#pragma unroll POND_ROW_UNROLL
-            for (int q = 0; q < NP; ++q) {
-#pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    if (G > 0 && p > 0 && p % G == 0) asm volatile("" ::: "memory");
-                    const P Wt = wx[p] * wy[q];
-                    P M[nmom_padded<P, L>()];
-                    load_moments<P, nmom<L>()>(lds, cap, base + q * rs + p, M);
-#pragma unroll
-                    for (int k = 0; k < L::NM; ++k) {
-                        Mf[k] += Wt * M[k];
-                        Mg[k] += Wt * M[L::NM + k];
-                    }
-                }
-            }
-        } else if (inside) {
-            // byte offsets: the region is under 2^24 bytes, so the products are
-            // 24-bit multiplies (full rate, where 32-bit ones take four cycles)
-            constexpr unsigned NB = lds_node_bytes<P, L>();
-            const unsigned rowb = flat_y ? 0u : unsigned(W) * NB;
-            unsigned row = __umul24(unsigned(flat_y ? 0 : by - Y0), rowb) +
-                           __umul24(unsigned(bx - X0), NB);
-            // every stencil row unrolled (its weight wy[q] is a register); a
-            // compiler barrier after each G taps bounds the loads in flight
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-#pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    if (G > 0 && (q > 0 || p > 0) && (q * NP + p) % G == 0)
-                        asm volatile("" ::: "memory");
-                    const P Wt = wx[p] * wy[q];
-                    P M[nmom_padded<P, L>()];
-                    load_node_lds_at<P, L>(lds, row + unsigned(p) * NB, M);
-#pragma unroll
-                    for (int k = 0; k < L::NM; ++k) {
-                        Mf[k] += Wt * M[k];
-                        Mg[k] += Wt * M[L::NM + k];
-                    }
-                }
-                row += rowb;
-            }
+    // A staged row from column bx: (k, p) is moment group k of the node in column
+    // bx + p; next() moves to the row above.  Byte offsets: the region is under 2^24
+    // bytes, so the products are 24-bit multiplies (full rate, where 32-bit ones take
+    // four cycles).
+    struct Row {
+        const char *base;
+        unsigned off, pitch;
+        int cap;
+        __device__ __forceinline__ V operator()(int k, int p) const {
+            if constexpr (lds_planar<P, L>())
+                return *reinterpret_cast<const V *>(base + off + unsigned(k * cap) * sizeof(V) +
+                                                    unsigned(p * sizeof(V)));
+            else
+                return *reinterpret_cast<const V *>(base + off +
+                                                    unsigned(p) * lds_node_bytes<P, L>() +
+                                                    unsigned(k * sizeof(V)));
+        }
+        __device__ __forceinline__ void next() { off += pitch; }
+    };
+    __device__ __forceinline__ Row staged(int bx, int r) const {
+        constexpr unsigned NB = lds_planar<P, L>() ? sizeof(V) : lds_node_bytes<P, L>();
+        const unsigned pitch = flat() ? 0u : unsigned(W) * NB;
+        return Row{reinterpret_cast<const char *>(lds),
+                   unsigned(__umul24(unsigned(flat() ? 0 : r - Y0), pitch)) +
+                       unsigned(__umul24(unsigned(bx - X0), NB)),
+                   pitch, cap};
+    }
+    // the moments of grid node (x, y), from the staged region or HBM
+    __device__ __forceinline__ void read(int x, int y, P *M) const {
+        if (inside(x, 1, y, 1)) {
+            const int idx = __umul24(unsigned(flat() ? 0 : y - Y0), unsigned(W)) + (x - X0);
+            load_node_lds<P, L>(lds, idx, cap, M);
         } else {
-            // the HBM gather's column indices depend on bx alone; the empty asm
-            // keeps the compiler from hoisting them out of the velocity loop into
-            // the path every lane runs
-            int bxv = bx;
-            asm volatile("" : "+v"(bxv));
-            glob.gather(bxv, by, wx, wy, Mf, Mg);
+            glob.read(x, y, M);
         }
     }
 };
 
-// Ints of shared memory per block_min of a block of NT lanes: one per wave, at
-// least four (blocks of up to 256 lanes keep a 16-int array; a larger static
-// array moves the dynamic LDS and costs the step kernel a register).
+// Ints of shared memory of block_bounds for a block of NT lanes: four per wave.
 template <int NT>
-constexpr int red_slots() {
-    return NT > 256 ? (NT + 63) / 64 : 4;
+constexpr int bound_slots() {
+    return 4 * ((NT + 63) / 64);
 }
 
-// Minimum over the block (at most 8 waves); red holds one int per wave.
-__device__ __forceinline__ int block_min(int v, int *red) {
+// Minimum over the wave, in every lane: data-parallel shifts within rows of 16
+// lanes, then across them (the last lane holds the result).
+__device__ __forceinline__ int wave_min(int v) {
+    constexpr int kMax = 0x7fffffff;
+    v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x111, 0xf, 0xf, false));  // row_shr:1
+    v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x112, 0xf, 0xf, false));  // row_shr:2
+    v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x114, 0xf, 0xf, false));  // row_shr:4
+    v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x118, 0xf, 0xf, false));  // row_shr:8
+    v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Minima of four values over the block (NT lanes, every one calling); one
+// barrier, none for a single wave.  red: bound_slots<NT>() ints.
+template <int NT>
+__device__ __forceinline__ void block_bounds(int (&v)[4], int *red) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
-    const int w = threadIdx.x / 64, nw = (blockDim.x + 63) / 64;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    __syncthreads();
-    int r = red[0];
-    for (int i = 1; i < nw; ++i) r = min(r, red[i]);
-    return r;
+    for (int k = 0; k < 4; ++k) v[k] = wave_min(v[k]);
+    if constexpr (NT > 64) {
+        const int w = int(threadIdx.x) / 64;
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) red[4 * w + k] = v[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            int r = red[k];
+#pragma unroll
+            for (int u = 1; u < NT / 64; ++u) r = min(r, red[4 * u + k]);
+            v[k] = __builtin_amdgcn_readfirstlane(r);
+        }
+    }
 }
 
-// Minimum waves per SIMD asked of the register allocator for the step kernels
-// of NT lanes per block (168 VGPRs allow three, 128 four).  FP32 asks for three:
-// the allocation sits at that boundary, and one register more halves the
-// waves that hide the LDS latency.  FP32 blocks of 512 lanes ask for four: two
-// such blocks share a CU's LDS, half of it each, which holds the source region
-// of a 32 x 16 tile of an advected flow, and a grid of 4096 waves (512^2
-// nodes) then runs in a single round.  FP64 holds two unforced (the internal
-// split, whose frame temperature takes the source's work, asks); D2Q25 keeps
-// the compiler's choice (two waves in FP32, one in FP64: more would spill).
+// Minimum waves per SIMD asked of the register allocator for the step kernels of
+// NT lanes per block.  FP32 D2Q16 needs 228 VGPRs: two waves (three, at 168 VGPRs,
+// spill 36 of them: 2048^2 quadrants 0.82 against 0.71 ms per step, 512^2 Mach 2
+// 0.117 against 0.113).  FP64 holds the weight table and a row in twice the
+// registers: one wave of 512 (two spill 130: 512^2 Mach 2 0.51 against 0.34 ms).
 template <typename P, int S, int NT = 256, class L = D2Q16>
 constexpr int step_min_waves() {
-    if (L::Q != 16) return shared_rows_transformed<P, L>() ? POND_D2Q25_SHARED_WAVES : 1;
-    if (sizeof(P) == 4) {
-        // the shared x-pass holds the coefficients and sums of a velocity group
-        // (250 VGPRs with groups of four): two waves
-        if (vel_group<P, L>() > 1) return 2;
-        return NT == 512 ? 4 : 3;
-    }
-    return S == 1 ? 2 : 1;
+    if (sizeof(P) == 4) return L::Q == 16 ? POND_WAVES_F32 : POND_WAVES_F32_25;
+    return L::Q == 16 ? POND_WAVES_F64 : POND_WAVES_F64_25;
 }
 
 // Blocks are dispatched round-robin over the 8 XCDs (block b on XCD b % 8);
@@ -261,14 +175,26 @@ __device__ __forceinline__ void band_tile(int t, int tiles_x, int tiles_y, int &
     }
 }
 
-// Tile shapes: TX x TY destination nodes, one lane each, lane t at (t % TX, t / TX).
+// Tile shapes: TX x TY destination nodes, one lane each: lane t at (t % TX, t / TX),
+// in 16-wide tiles within pairs of rows so that the lanes which a 16-byte LDS
+// read serves together -- 0-3, 12-15, 20-23 and 24-27 of each 32, and the other
+// sixteen -- are those of one row: neighbouring staged nodes, which lie on
+// different banks, where two rows' would share some (2048^2 quadrants, 16 x 8
+// tiles in row order: 47 % of the LDS cycles were conflicts).
+__device__ __forceinline__ int pair_row(int t) {  // of lane t, 0 or 1
+    return (0x96 >> ((t >> 2) & 7)) & 1;          // odd parity of its group of four
+}
+__device__ __forceinline__ int pair_column(int t) { return ((t >> 1) & 12) | (t & 3); }
+
 template <int TX, int TY>
 struct FixedShape {
     static constexpr int kThreads = TX * TY;
     __device__ __forceinline__ int tx() const { return TX; }
     __device__ __forceinline__ int ty() const { return TY; }
-    __device__ __forceinline__ int lx(int t) const { return t % TX; }
-    __device__ __forceinline__ int ly(int t) const { return t / TX; }
+    __device__ __forceinline__ int lx(int t) const { return TX == 16 ? pair_column(t) : t % TX; }
+    __device__ __forceinline__ int ly(int t) const {
+        return TX == 16 ? 2 * (t / 32) + pair_row(t) : t / TX;
+    }
 };
 // 256 lanes, TX = 2^lg, TY = 256 / TX.
 struct Shape256 {
@@ -276,8 +202,12 @@ struct Shape256 {
     int lg;
     __device__ __forceinline__ int tx() const { return 1 << lg; }
     __device__ __forceinline__ int ty() const { return 256 >> lg; }
-    __device__ __forceinline__ int lx(int t) const { return t & ((1 << lg) - 1); }
-    __device__ __forceinline__ int ly(int t) const { return t >> lg; }
+    __device__ __forceinline__ int lx(int t) const {
+        return lg == 4 ? pair_column(t) : t & ((1 << lg) - 1);
+    }
+    __device__ __forceinline__ int ly(int t) const {
+        return lg == 4 ? 2 * (t >> 5) + pair_row(t) : t >> lg;
+    }
 };
 
 // Source region of a tile: the union [X0, X1] x [Y0, Y1] of its lanes'
@@ -317,7 +247,7 @@ __device__ __forceinline__ void clip_region(int tx0, int ty0, int tx, int ty, in
 // The tile with first node (tx0, ty0): load the time-t frames, bound the
 // source region (clip_region), stage the region's moments, then run every
 // lane's node step (energy split S, lattice L).  Every thread of the block must
-// call it (it synchronises the block).  red: 4 red_slots<Shape::kThreads>()
+// call it (it synchronises the block).  red: bound_slots<Shape::kThreads>()
 // ints of shared memory.
 template <typename P, int NP, int S, class L, class Shape>
 __device__ __forceinline__ void tile_step(const StepArgs &a, DevState src, const P *__restrict__ mom,
@@ -342,33 +272,46 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, DevState src, const
         stencil_extent<NP, L>(y, l1, s, ly, hy);
     }
     const bool flat_y = a.ny == 1 && a.bc_y != 2;  // walls: the ghost rows differ
-    constexpr int RS = red_slots<Shape::kThreads>();
-    int X0 = block_min(lx, red);
-    int X1 = -block_min(-hx, red + RS);
-    int Y0 = block_min(ly, red + 2 * RS);
-    int Y1 = -block_min(-hy, red + 3 * RS);
+    int bound[4] = {lx, -hx, ly, -hy};
+    block_bounds<Shape::kThreads>(bound, red);
+    int X0 = bound[0], X1 = -bound[1], Y0 = bound[2], Y1 = -bound[3];
     clip_region(tx0, ty0, sh.tx(), sh.ty(), cap, flat_y, X0, X1, Y0, Y1);
     const int W = X1 >= X0 ? X1 - X0 + 1 : 0;
     const int H = Y1 >= Y0 ? Y1 - Y0 + 1 : 0;
 
     // the tile's reference moments (every node of the tile shares its block)
     GlobalTaps<P, NP, L> glob{mom, a.mstride, a.nx, a.ny, a.bc_x, a.bc_y, a.moff, a.wall_h, {}};
-    load_moments<P, nmom<L>()>(mom, a.mstride, a.moff + ref_node(tx0, ty0, a.nx), glob.ref);
+    glob.set_reference(tx0, ty0);
 
-    for (int idx = threadIdx.x; idx < W * H; idx += nthreads) {
-        const int gx = wrap_index(X0 + idx % W, a.nx, a.bc_x);
-        const int gy = mom_row(Y0 + idx / W, a.ny, a.bc_y, a.wall_h);
-        P M[nmom_padded<P, L>()];
-        load_moments<P, nmom<L>()>(mom, a.mstride, a.moff + (long long)gy * a.nx + gx, M);
+    // kStage nodes per lane at a time, their loads in flight together; rows and
+    // columns by a multiplication with 2^32 / W (exact: the region holds few nodes)
+    constexpr int kStage = sizeof(P) == 4 ? 3 : 2;
+    const int count = W * H;
+    const unsigned inv = W > 1 ? 0xffffffffu / unsigned(W) + 1u : 0u;
+    for (int base = int(threadIdx.x); base < count; base += kStage * nthreads) {
+        P M[kStage][nmom_padded<P, L>()];
 #pragma unroll
-        for (int k = 0; k < nmom<L>(); ++k) M[k] -= glob.ref[k];
-        store_node_lds<P, L>(lds, idx, cap, M);
+        for (int u = 0; u < kStage; ++u) {
+            const int idx = min(base + u * nthreads, count - 1);
+            const int row = W > 1 ? int(__umulhi(unsigned(idx), inv)) : idx;
+            const int gx = wrap_index(X0 + idx - row * W, a.nx, a.bc_x);
+            const int gy = mom_row(Y0 + row, a.ny, a.bc_y, a.wall_h);
+            load_moments<P, nmom<L>()>(mom, a.mstride, a.moff + (long long)gy * a.nx + gx, M[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kStage; ++u) {
+            const int idx = base + u * nthreads;
+            if (idx >= count) break;
+            if constexpr (deviations<P>()) {
+#pragma unroll
+                for (int k = 0; k < nmom<L>(); ++k) M[u][k] -= glob.ref[k];
+            }
+            store_node_lds<P, L>(lds, idx, cap, M[u]);
+        }
     }
     __syncthreads();
 
-    constexpr int G = sizeof(P) == 4 && Shape::kThreads == 512 ? 1
-                      : (sizeof(P) == 8 ? POND_TAP_GROUP_F64 : POND_TAP_GROUP_F32);
-    const TileTaps<P, NP, L, G> taps{lds, cap, X0, Y0, X1, Y1, W, flat_y, glob};
+    const TileTaps<P, NP, L> taps{lds, cap, X0, Y0, X1, Y1, W, glob};
     node_step<P, NP, S, L>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
 }
 
@@ -378,33 +321,32 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, DevState src, const
 template <typename P, class L = D2Q16>
 __device__ __forceinline__ void node_moments(const StepArgs &a, DevState st, P *__restrict__ mom,
                                              long long n) {
-    const P s = P(sqrt(st.T[n]));
+    double sd, isd;
+    frame_scale(st.T[n], sd, isd);
+    const P s = P(sd);
     const P dx = P(st.ux[n] - a.uref_x), dy = P(st.uy[n] - a.uref_y);
     constexpr int NM = L::NM;
     P M[nmom_padded<P, L>()];
 #pragma unroll
     for (int k = 0; k < nmom_padded<P, L>(); ++k) M[k] = P(0);
     // through the lattice sums, in the order the step forms them (the same bits)
-    P Cf[NM], Cg[NM], Sf[L::N + 1], Sg[L::N + 1];
+    P Cf[NM], Cg[NM];
 #pragma unroll
     for (int k = 0; k < NM; ++k) Cf[k] = Cg[k] = P(0);
-#pragma unroll
-    for (int q = 0; q <= L::N; ++q) Sf[q] = Sg[q] = P(0);
     double mass = 0.0, gzero = 0.0;  // zeroth moments summed in FP64, as the step does
 #pragma unroll
     for (int ia = 0; ia < L::Q1; ++ia) {
+        P fc[L::Q1], gc[L::Q1];
 #pragma unroll
         for (int b = 0; b < L::Q1; ++b) {
             const int i = L::Q1 * ia + b;
-            const P fi = pop_plane<P>(st.f, i, a.N)[n];
-            const P gi = pop_plane<P>(st.g, i, a.N)[n];
-            mass += double(fi);
-            gzero += double(gi);
-            column_add<L>(Sf, b, fi);
-            column_add<L>(Sg, b, gi);
+            fc[b] = pop_plane<P>(st.f, i, a.N)[n];
+            gc[b] = pop_plane<P>(st.g, i, a.N)[n];
+            mass += double(fc[b]);
+            gzero += double(gc[b]);
         }
-        column_flush<L>(Cf, Sf, ia);
-        column_flush<L>(Cg, Sg, ia);
+        column_add<L>(Cf, fc, ia);
+        column_add<L>(Cg, gc, ia);
     }
     moments_from_lattice_sums<L>(Cf, s, dx, dy, M);
     moments_from_lattice_sums<L>(Cg, s, dx, dy, M + NM);
