@@ -110,9 +110,16 @@ pond_status write_counters(pond_ctx *c, const DevCounters &in) {
 // one in FP64 with the cubic stencil); the LDS of a CU is split between the
 // blocks that fit by registers.  A 32 x 8 tile at T = 1, Mach 2 needs a
 // 40 x 16 source region.
-int default_lds_nodes(int tile, bool dbl, int np, int split, int lattice) {
+int default_lds_nodes(int tile, const pond_params &p) {
+    const bool dbl = p.precision == POND_PREC_FP64;
+    const bool quad = p.lattice == POND_LATTICE_D2Q16 &&
+                      (tile == POND_TILE_8x8 || tile == POND_TILE_64x1) &&
+                      quad_lanes((long long)p.nx * p.ny, dbl);
     return lds_nodes_for_blocks(
-        tiled_blocks_per_cu(lattice, dbl, np, split, static_cast<TileShape>(tile)), dbl, lattice);
+        quad ? quad_blocks_per_cu(dbl)
+             : tiled_blocks_per_cu(p.lattice, dbl, p.interp_points, p.split,
+                                   static_cast<TileShape>(tile)),
+        dbl, p.lattice);
 }
 
 // Compute units of the current device (0 if the query fails).
@@ -174,14 +181,15 @@ pond_tuning default_tuning(const pond_params &p, int reach) {
     // Mach 2: 545 against 495 MLUPS with 32 x 8)
     if (p.lattice == POND_LATTICE_D2Q25 && p.ny >= 16) t.tile = POND_TILE_16x16;
     if (small) t.tile = POND_TILE_16x8;
-    t.lds_nodes =
-        default_lds_nodes(t.tile, p.precision == POND_PREC_FP64, p.interp_points, p.split,
-                          p.lattice);
+    // small D2Q16 grids: 64-node tiles, four lanes per node
+    const bool quad = p.lattice == POND_LATTICE_D2Q16 && quad_lanes((long long)p.nx * p.ny, dbl);
+    if (quad && p.ny >= 8) t.tile = POND_TILE_8x8;
+    t.lds_nodes = default_lds_nodes(t.tile, p);
     // FP64 moments take twice the LDS: measured at 512^2, Mach 2, one 32 x 8
     // block per CU holding its whole 40 x 16 source region beats two blocks
     // that fall back to HBM for part of the taps (527 vs 323 MLUPS); a 32 x 16
     // block fills one CU by its registers alone
-    if (dbl && p.ny >= 8 && !small && p.lattice == POND_LATTICE_D2Q16)
+    if (dbl && p.ny >= 8 && !small && !quad && p.lattice == POND_LATTICE_D2Q16)
         t.lds_nodes = lds_nodes_for_blocks(1, true);
     t.batch_tile_width = 0;
     return t;
@@ -298,8 +306,7 @@ pond_status apply_tuning(pond_ctx *c, const pond_tuning &t) {
         return fail(POND_ERR_UNSUPPORTED, "the 32 x 16 tile is built for D2Q16 only");
     pond_tuning u = t;
     if (u.lds_nodes <= 0)
-        u.lds_nodes =
-            default_lds_nodes(u.tile, fp64(c), c->p.interp_points, c->p.split, c->p.lattice);
+        u.lds_nodes = default_lds_nodes(u.tile, c->p);
     const size_t bytes = size_t(u.lds_nodes) * lds_node_values(c->p.lattice, fp64(c)) * c->psize;
     if (bytes > 159 * 1024)  // one KiB stays for the static shared memory
         return fail(POND_ERR_INVALID_ARG, "lds_nodes %d needs %zu bytes of LDS (> 159 KiB)",

@@ -65,7 +65,7 @@ Layout layout_for(long long N, size_t psize, int lattice, long long mom_nodes, i
 // blocks_per_cu blocks share the 160 KiB of a CU.
 int lds_nodes_for_blocks(int blocks_per_cu, bool dbl, int lattice = 16);
 // LDS nodes per block of the tiled kernel's default share for a tile shape.
-int default_lds_nodes(int tile, bool dbl, int np, int split, int lattice);
+int default_lds_nodes(int tile, const pond_params &p);
 // Default launch configuration of a context with these parameters (on the
 // current device); reach: the stencil reach of its initial frame in nodes, 0 if
 // it is not known.

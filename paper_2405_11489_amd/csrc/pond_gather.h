@@ -395,7 +395,9 @@ __device__ __forceinline__ void gather_general(const Taps &taps, int ia, double 
 // (very hot flows) is visited stencil by stencil.  The sums are the same numbers either way: each velocity's rows
 // are added in ascending order, the others add zero.  On a single-row grid
 // every stencil row is that row, and the weights sum to one.
-template <typename P, int NP, class L, class Taps, class Column>
+//
+// Quad: this lane gathers x-component threadIdx.x % 4 alone.
+template <typename P, int NP, class L, bool Quad, class Taps, class Column>
 __device__ __forceinline__ void gather_rows(const Taps &taps, double xu, double yu, double sc,
                                             P dux, P duy, P is, P T, Column &column) {
     constexpr int NM = L::NM, Q1 = L::Q1, RS = table_rows<NP>();
@@ -424,8 +426,7 @@ __device__ __forceinline__ void gather_rows(const Taps &taps, double xu, double 
             for (int r = 0; r < RS; ++r) wt[r][b] = t[r];
             if (flat) wt[0][b] = P(1);
         }
-#pragma unroll 1
-        for (int ia = 0; ia < Q1; ++ia) {
+        auto component = [&](int ia) {
             P wx[NP], al[NM], af[Q1], ag[Q1];
             const int bx = lagrange<NP>(fma(-sc, L::c(ia), xu), wx);
             xf.factors(tab.kap[ia], al);
@@ -436,13 +437,24 @@ __device__ __forceinline__ void gather_rows(const Taps &taps, double xu, double 
             rd.load(at, 0);
             unrolled_rows<0, RS>(rd, at, span, flat, wx, al, y, wt, af, ag);
             column(ia, af, ag);
+        };
+        if constexpr (Quad) {
+            component(int(threadIdx.x) & 3);
+        } else {
+#pragma unroll 1
+            for (int ia = 0; ia < Q1; ++ia) component(ia);
         }
     } else {
-#pragma unroll 1
-        for (int ia = 0; ia < Q1; ++ia) {
+        auto component = [&](int ia) {
             P f[Q1], g[Q1];
             gather_general<P, NP, L>(taps, ia, xu, yu, sc, xf, y, f, g);
             column(ia, f, g);
+        };
+        if constexpr (Quad) {
+            component(int(threadIdx.x) & 3);
+        } else {
+#pragma unroll 1
+            for (int ia = 0; ia < Q1; ++ia) component(ia);
         }
     }
 }

@@ -98,6 +98,20 @@ inline void tile_dims(TileShape s, int &tx, int &ty) {
     tx = ty = 0;
 }
 
+// Whether the 64-node tiles (8 x 8, 64 x 1) of a D2Q16 grid of N nodes run four
+// lanes per node.  One lane per node leaves such a grid a few waves on part of the
+// CUs, each working through its node's x-components in turn; four lanes take a
+// step to half the time or less until the blocks of 256 lanes need more than one
+// or two rounds of the chip (two per CU in FP32, one in FP64).  Milliseconds per
+// step with them / with the best other tile, Mach 2 and quadrants: FP32 64^2
+// 0.019 / 0.042 and 0.021 / 0.043, 160^2 0.025 / 0.043 and 0.025 / 0.047, 192^2
+// 0.038 / 0.045 and 0.033 / 0.048, 256^2 0.046 / 0.048 and 0.045 / 0.050; FP64
+// 64^2 0.035 / 0.094 and 0.034 / 0.086, 160^2 0.067 / 0.094 and 0.060 / 0.088,
+// 192^2 0.086 / 0.101 and 0.072 / 0.089, 256^2 0.113 / 0.084 and 0.102 / 0.089.
+inline bool quad_lanes(long long N, bool dbl) { return N <= (dbl ? 36864 : 49152); }
+// Blocks per CU of the four-lane kernels by registers (the LDS share of a block).
+inline int quad_blocks_per_cu(bool dbl) { return dbl ? 1 : 2; }
+
 // Blocks of the tiled step kernel (lattice, precision, stencil, energy split,
 // shape) that fit one CU by registers and waves alone (no dynamic LDS).
 int tiled_blocks_per_cu(int lattice, bool dbl, int np, int split, TileShape shape);

@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kBlock) void step_kernel(StepArgs a, DevState src,
     }
     GlobalTaps<P, NP, L> taps{mom, a.mstride, a.nx, a.ny, a.bc_x, a.bc_y, a.moff, a.wall_h, {}};
     taps.set_reference(x, y);
-    node_step<P, NP, S, L>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
+    node_step<P, NP, S, L, false>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
 }
 
 // ------------------------------------------------------ step (LDS tiles) ----
@@ -130,6 +130,20 @@ __global__ __launch_bounds__(TX *TY) POND_TILED_ATTR(P, S, TX *TY, L) void step_
     band_tile<TX>(xcd_tile(blockIdx.x, gridDim.x), tiles_x, int(gridDim.x) / tiles_x, tx, ty);
     tile_step<P, NP, S, L>(a, src, mom, dst, mom_out, cnt, reinterpret_cast<P *>(smem_raw), cap,
                            tx * TX, ty * TY, FixedShape<TX, TY>{}, red);
+}
+
+// Four lanes per node (node_step's Quad): blocks of 64 nodes, 8 x 8 or 64 x 1, 256
+// lanes.
+template <typename P, int NP, int S, class L, int TX, int TY>
+__global__ __launch_bounds__(4 * TX * TY) POND_TILED_ATTR(P, S, 4 * TX * TY, L) void step_quad_kernel(
+    StepArgs a, DevState src, const P *__restrict__ mom, DevState dst, P *__restrict__ mom_out,
+    DevCounters *cnt, int cap, int tiles_x) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ int red[bound_slots<4 * TX * TY>()];
+    int tx, ty;
+    band_tile<TX>(xcd_tile(blockIdx.x, gridDim.x), tiles_x, int(gridDim.x) / tiles_x, tx, ty);
+    tile_step<P, NP, S, L, true>(a, src, mom, dst, mom_out, cnt, reinterpret_cast<P *>(smem_raw),
+                                 cap, tx * TX, ty * TY, FixedShape<TX, TY>{}, red);
 }
 
 // ------------------------------------------------------ wall ghosts ----
@@ -358,15 +372,22 @@ const void *tiled_kernel_ptr(TileShape shape) {
 template <typename P, int NP, int S, class L, int TX, int TY>
 hipError_t launch_tiled_t(const StepArgs &a, const TileConfig &tc, DevState src, const P *mom,
                           DevState dst, P *mom_out, DevCounters *cnt, hipStream_t s) {
+    const int tiles_x = (a.nx + TX - 1) / TX, tiles_y = (a.ny + TY - 1) / TY;
     auto kern = step_tiled_kernel<P, NP, S, L, TX, TY>;
+    int lanes = TX * TY;
+    if constexpr (L::Q1 == 4 && TX * TY == 64) {
+        if (quad_lanes(a.N, sizeof(P) == 8)) {
+            kern = step_quad_kernel<P, NP, S, L, TX, TY>;
+            lanes = 4 * TX * TY;
+        }
+    }
     const size_t lds = size_t(tc.cap) * lds_stride<P, L>() * (16 / sizeof(P)) * sizeof(P);
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
         if (e != hipSuccess) return e;
     }
-    const int tiles_x = (a.nx + TX - 1) / TX, tiles_y = (a.ny + TY - 1) / TY;
-    hipLaunchKernelGGL(kern, dim3(tiles_x * tiles_y), dim3(TX * TY), lds, s, a, src, mom, dst,
+    hipLaunchKernelGGL(kern, dim3(tiles_x * tiles_y), dim3(lanes), lds, s, a, src, mom, dst,
                        mom_out, cnt, tc.cap, tiles_x);
     return hipGetLastError();
 }

@@ -317,6 +317,21 @@ struct GlobalTaps {
     __device__ __forceinline__ Row staged(int, int) const { return Row{}; }
 };
 
+// Four lanes per node (Quad kernels): lane j of a group of four holds x-component
+// j's share.  quad_lane(v, j): the value of the group's lane j.
+template <int J>
+__device__ __forceinline__ int quad_lane(int v) {
+    return __builtin_amdgcn_mov_dpp(v, J * 0x55, 0xf, 0xf, true);  // quad_perm [J, J, J, J]
+}
+template <int J>
+__device__ __forceinline__ float quad_lane(float v) {
+    return __int_as_float(quad_lane<J>(__float_as_int(v)));
+}
+template <int J>
+__device__ __forceinline__ double quad_lane(double v) {
+    return __hiloint2double(quad_lane<J>(__double2hiint(v)), quad_lane<J>(__double2loint(v)));
+}
+
 // Lanes of the wave for which c holds (a ballot and a scalar bit count).
 __device__ __forceinline__ unsigned long long wave_count(bool c) {
     return (unsigned long long)__popcll(__ballot(c));
@@ -325,16 +340,15 @@ __device__ __forceinline__ unsigned long long wave_count(bool c) {
 // Moments sum_i f_i V_ix^p V_iy^q of Q populations at the velocities V_i =
 // s c_i + d (c_i = (c(a), c(b)) for i = Q1 a + b; one scale s and offset d for
 // all i) through the lattice sums C_pq = sum_i f_i c(a)^p c(b)^q, which the
-// x-components build in turn: column_add takes the populations f[0..Q1) of
-// x-component a into S_q = sum_b f_b c(b)^q (the even and odd parts of +-c(b)
-// first) and adds c(a)^p S_q to C_pq; moments_from_lattice_sums expands
+// x-components build in turn: column_sums takes the populations f[0..Q1) of an
+// x-component into S_q = sum_b f_b c(b)^q (the even and odd parts of +-c(b) first),
+// column_flush adds c(a)^p S_q to C_pq; moments_from_lattice_sums expands
 // (s c + d)^p by the binomial theorem at the end.  (Three operations per
 // population and NM per x-component, where the monomials of each V_i and their
 // products with f_i cost about 3 NM.)  Weighted: the populations come over
 // their weights w(a) w(b).
 template <class L, bool Weighted = false, typename P>
-__device__ __forceinline__ void column_add(P C[L::NM], const P f[L::Q1], int a) {
-    P S[L::N + 1];
+__device__ __forceinline__ void column_sums(const P f[L::Q1], P S[L::N + 1]) {
 #pragma unroll
     for (int h = 0; h < L::Q1 / 2; ++h) {
         const double cb = L::c(L::Q1 - 1 - h);
@@ -352,6 +366,9 @@ __device__ __forceinline__ void column_add(P C[L::NM], const P f[L::Q1], int a) 
     }
     if constexpr (L::Q1 % 2 == 1)  // the zero abscissa
         S[0] += Weighted ? P(L::w(L::Q1 / 2)) * f[L::Q1 / 2] : f[L::Q1 / 2];
+}
+template <class L, bool Weighted = false, typename P>
+__device__ __forceinline__ void column_flush(P C[L::NM], const P S[L::N + 1], int a) {
     const P ca = P(L::c(a));
     P cp = Weighted ? P(L::w(a)) : P(1);
 #pragma unroll
@@ -361,6 +378,12 @@ __device__ __forceinline__ void column_add(P C[L::NM], const P f[L::Q1], int a) 
             C[mom_index(p, q)] += p == 0 && !Weighted ? S[q] : cp * S[q];
         cp *= ca;
     }
+}
+template <class L, typename P>
+__device__ __forceinline__ void column_add(P C[L::NM], const P f[L::Q1], int a) {
+    P S[L::N + 1];
+    column_sums<L>(f, S);
+    column_flush<L>(C, S, a);
 }
 
 template <class L, typename P>
@@ -512,7 +535,13 @@ namespace pond {
 // FP64 sums rho, j, E and the lattice sums of the gathered populations (their
 // lab moments follow once, from the last gather's) are accumulated on the fly,
 // so no population array is kept.
-template <typename P, int NP, int S, class L, class Taps>
+//
+// Quad: four lanes share the node (every argument alike), one per x-component:
+// each gathers and reconstructs its own x-component, and the sums over the
+// x-components are formed by every lane, in the order of the loop over them, so
+// the bits are those of one lane per node.  Small grids, whose few waves leave
+// most of the chip idle, take a quarter of the gather's time per step this way.
+template <typename P, int NP, int S, class L, bool Quad, class Taps>
 __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, int x, int y,
                                           long long n, bool live, double l0, double l1, double l2,
                                           const DevState &src, DevState dst,
@@ -527,6 +556,8 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
 #pragma unroll
     for (int k = 0; k < NM; ++k) Mf[k] = Mg[k] = Cf[k] = Cg[k] = P(0);
     bool done = !live, conv = false, bad = false, overrun = false;
+    const int quad = Quad ? int(threadIdx.x) & 3 : 0;
+    const bool owner = quad == 0;  // the lane that counts its node
     unsigned long long itc = 0;  // gathers of the wave's lanes
     // internal split: the source's velocity gradient (the same for every
     // iterate), in the arithmetic's precision
@@ -558,7 +589,7 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
     };
 
     for (int it = 0; it < a.pc_max_iter; ++it) {
-        itc += wave_count(!done);
+        itc += wave_count(!done && owner);
         if (!done) {
             double s, isd;
             frame_scale(lg2, s, isd);
@@ -582,8 +613,19 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
             for (int k = 0; k < NM; ++k) Cf[k] = Cg[k] = P(0);
             // x-component ia's populations gathered in the iterate frame, over their
             // weights: the FP64 sums of f, f c and g (and f |c|^2), and the lattice sums
-            auto column = [&](int ia, const P (&f)[L::Q1], const P (&g)[L::Q1]) {
+            auto add = [&](int ia, double s0, double s1, double s2, double sg,
+                           const P (&Sf)[L::N + 1], const P (&Sg)[L::N + 1]) {
                 const double ca = L::c(ia), wa = gather_weight<P, L>(ia);
+                s0 *= wa;
+                r += s0;
+                mx += ca * s0;
+                my += wa * s1;
+                if constexpr (S == 2) m2 += ca * ca * s0 + wa * s2;
+                Eg += wa * sg;
+                column_flush<L, true>(Cf, Sf, ia);
+                column_flush<L, true>(Cg, Sg, ia);
+            };
+            auto column = [&](int ia, const P (&f)[L::Q1], const P (&g)[L::Q1]) {
                 double s0 = 0.0, s1 = 0.0, s2 = 0.0, sg = 0.0;
 #pragma unroll
                 for (int b = 0; b < L::Q1; ++b) {
@@ -594,16 +636,30 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
                     if constexpr (S == 2) s2 += (wb * cb * cb) * fd;
                     sg += wb * double(g[b]);
                 }
-                s0 *= wa;
-                r += s0;
-                mx += ca * s0;
-                my += wa * s1;
-                if constexpr (S == 2) m2 += ca * ca * s0 + wa * s2;
-                Eg += wa * sg;
-                column_add<L, true>(Cf, f, ia);
-                column_add<L, true>(Cg, g, ia);
+                P Sf[L::N + 1], Sg[L::N + 1];
+                column_sums<L, true>(f, Sf);
+                column_sums<L, true>(g, Sg);
+                if constexpr (Quad) {
+                    auto from = [&](auto lane) {
+                        constexpr int J = decltype(lane)::value;
+                        P Tf[L::N + 1], Tg[L::N + 1];
+#pragma unroll
+                        for (int q = 0; q <= L::N; ++q) {
+                            Tf[q] = quad_lane<J>(Sf[q]);
+                            Tg[q] = quad_lane<J>(Sg[q]);
+                        }
+                        add(J, quad_lane<J>(s0), quad_lane<J>(s1),
+                            S == 2 ? quad_lane<J>(s2) : 0.0, quad_lane<J>(sg), Tf, Tg);
+                    };
+                    from(std::integral_constant<int, 0>{});
+                    from(std::integral_constant<int, 1>{});
+                    from(std::integral_constant<int, 2>{});
+                    from(std::integral_constant<int, 3>{});
+                } else {
+                    add(ia, s0, s1, s2, sg, Sf, Sg);
+                }
             };
-            gather_rows<P, NP, L>(taps, xu, yu, sc, dux, duy, is, P(sr * sr), column);
+            gather_rows<P, NP, L, Quad>(taps, xu, yu, sc, dux, duy, is, P(sr * sr), column);
             // momentum, and in the non-translational split the energy f carries, at
             // the velocities C = s c + u of the iterate frame
             double jx = sr * mx + lg0 * r, jy = sr * my + lg1 * r, E = Eg;
@@ -800,9 +856,8 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
 #pragma unroll
         for (int k = 0; k < NM; ++k) Nf[k] = Ng[k] = P(0);
         double mass = 0.0, gzero = 0.0;  // zeroth moments summed in FP64 (see above)
-#pragma unroll 1
-        for (int ia = 0; ia < L::Q1; ++ia) {
-            P fc[L::Q1], gc[L::Q1];
+        // x-component ia's post-collision populations, stored
+        auto rebuild = [&](int ia, P (&fc)[L::Q1], P (&gc)[L::Q1]) {
 #pragma unroll
             for (int b = 0; b < L::Q1; ++b) {
                 const int i = L::Q1 * ia + b;
@@ -824,32 +879,64 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
                 out_store<kStreamPops>(&pop_plane<P>(dst.g, i, a.N)[n], gv);
                 fc[b] = fv;
                 gc[b] = gv;
-                mass += double(fv);
-                gzero += double(gv);
+            }
+        };
+        auto gather_sums = [&](int ia, const P (&fc)[L::Q1], const P (&gc)[L::Q1]) {
+#pragma unroll
+            for (int b = 0; b < L::Q1; ++b) {
+                mass += double(fc[b]);
+                gzero += double(gc[b]);
             }
             column_add<L>(Nf, fc, ia);
             column_add<L>(Ng, gc, ia);
+        };
+        if constexpr (Quad) {
+            P fc[L::Q1], gc[L::Q1];
+            rebuild(quad, fc, gc);
+            auto from = [&](auto lane) {
+                constexpr int J = decltype(lane)::value;
+                P fj[L::Q1], gj[L::Q1];
+#pragma unroll
+                for (int b = 0; b < L::Q1; ++b) {
+                    fj[b] = quad_lane<J>(fc[b]);
+                    gj[b] = quad_lane<J>(gc[b]);
+                }
+                gather_sums(J, fj, gj);
+            };
+            from(std::integral_constant<int, 0>{});
+            from(std::integral_constant<int, 1>{});
+            from(std::integral_constant<int, 2>{});
+            from(std::integral_constant<int, 3>{});
+        } else {
+#pragma unroll 1
+            for (int ia = 0; ia < L::Q1; ++ia) {
+                P fc[L::Q1], gc[L::Q1];
+                rebuild(ia, fc, gc);
+                gather_sums(ia, fc, gc);
+            }
         }
         moments_from_lattice_sums<L>(Nf, sM, dxM, dyM, MM);
         moments_from_lattice_sums<L>(Ng, sM, dxM, dyM, MM + NM);
         MM[0] = P(mass);
         MM[NM] = P(gzero);
-        out_store<kStreamFrame>(&dst.ux[n], uxst);
-        out_store<kStreamFrame>(&dst.uy[n], uyst);
-        out_store<kStreamFrame>(&dst.T[n], Tst);
-        if constexpr (S == 1) {
-            // the time-t frame becomes the new state's previous level (read again
-            // rather than kept live across the loop)
-            out_store<kStreamFrame>(&dst.uxp[n], src.ux[n]);
-            out_store<kStreamFrame>(&dst.uyp[n], src.uy[n]);
+        if (owner) {
+            out_store<kStreamFrame>(&dst.ux[n], uxst);
+            out_store<kStreamFrame>(&dst.uy[n], uyst);
+            out_store<kStreamFrame>(&dst.T[n], Tst);
+            if constexpr (S == 1) {
+                // the time-t frame becomes the new state's previous level (read again
+                // rather than kept live across the loop)
+                out_store<kStreamFrame>(&dst.uxp[n], src.ux[n]);
+                out_store<kStreamFrame>(&dst.uyp[n], src.uy[n]);
+            }
+            store_moments_out<P, nmom<L>()>(mom_out, a.mstride, a.moff + n, MM);
         }
-        store_moments_out<P, nmom<L>()>(mom_out, a.mstride, a.moff + n, MM);
     }
 
     // counters: one atomic per wave
-    const unsigned long long nc = wave_count(live && !conv && !bad);
-    const unsigned long long nb = wave_count(live && bad);
-    const unsigned long long no = wave_count(live && overrun);
+    const unsigned long long nc = wave_count(live && owner && !conv && !bad);
+    const unsigned long long nb = wave_count(live && owner && bad);
+    const unsigned long long no = wave_count(live && owner && overrun);
     if ((threadIdx.x & 63) == 0) {
         DevCounters::Slot *slot = &cnt->slot[blockIdx.x % kCounterSlots];
         if (itc) atomicAdd(&slot->pc_iterations, itc);

@@ -246,15 +246,17 @@ __device__ __forceinline__ void clip_region(int tx0, int ty0, int tx, int ty, in
 
 // The tile with first node (tx0, ty0): load the time-t frames, bound the
 // source region (clip_region), stage the region's moments, then run every
-// lane's node step (energy split S, lattice L).  Every thread of the block must
-// call it (it synchronises the block).  red: bound_slots<Shape::kThreads>()
-// ints of shared memory.
-template <typename P, int NP, int S, class L, class Shape>
+// lane's node step (energy split S, lattice L; Quad: four lanes per node, so a
+// block of four times the tile's lanes).  Every thread of the block must
+// call it (it synchronises the block).  red: bound_slots ints
+// of shared memory for the block's lanes.
+template <typename P, int NP, int S, class L, bool Quad = false, class Shape>
 __device__ __forceinline__ void tile_step(const StepArgs &a, DevState src, const P *__restrict__ mom,
                                           DevState dst, P *__restrict__ mom_out, DevCounters *cnt,
                                           P *lds, int cap, int tx0, int ty0, Shape sh, int *red) {
-    const int nthreads = sh.tx() * sh.ty();
-    const int x = tx0 + sh.lx(int(threadIdx.x)), y = ty0 + sh.ly(int(threadIdx.x));
+    constexpr int kLanes = Quad ? 4 : 1;  // per node
+    const int nthreads = kLanes * sh.tx() * sh.ty(), t = int(threadIdx.x) / kLanes;
+    const int x = tx0 + sh.lx(t), y = ty0 + sh.ly(t);
     const bool live = x < a.nx && y < a.ny;
     const long long n = live ? (long long)y * a.nx + x : 0;
     double l0 = 0.0, l1 = 0.0, l2 = 1.0;
@@ -273,7 +275,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, DevState src, const
     }
     const bool flat_y = a.ny == 1 && a.bc_y != 2;  // walls: the ghost rows differ
     int bound[4] = {lx, -hx, ly, -hy};
-    block_bounds<Shape::kThreads>(bound, red);
+    block_bounds<kLanes * Shape::kThreads>(bound, red);
     int X0 = bound[0], X1 = -bound[1], Y0 = bound[2], Y1 = -bound[3];
     clip_region(tx0, ty0, sh.tx(), sh.ty(), cap, flat_y, X0, X1, Y0, Y1);
     const int W = X1 >= X0 ? X1 - X0 + 1 : 0;
@@ -312,7 +314,7 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, DevState src, const
     __syncthreads();
 
     const TileTaps<P, NP, L> taps{lds, cap, X0, Y0, X1, Y1, W, glob};
-    node_step<P, NP, S, L>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
+    node_step<P, NP, S, L, Quad>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
 }
 
 // Moments up to the lattice's Grad order (three on D2Q16, four on D2Q25) of
