@@ -374,10 +374,7 @@ pond_status finish_init(pond_ctx *c, const DevCounters &h) {
     return apply_tuning(c, t);
 }
 
-pond_status set_reference_from_counters(pond_ctx *c) {
-    DevCounters h;
-    pond_status s = read_counters(c, &h);
-    if (s != POND_OK) return s;
+pond_status set_reference(pond_ctx *c, const DevCounters &h) {
     if (!(h.partial[0] > 0.0)) return fail(POND_ERR_INVALID_ARG, "total mass is not positive");
     c->args.uref_x = h.partial[1] / h.partial[0];
     c->args.uref_y = h.partial[2] / h.partial[0];
@@ -548,11 +545,9 @@ pond_status pond_init_fields(pond_ctx *c, const double *rho, const double *ux, c
     hipError_t e = fp64(c) ? launch_init_t<double>(c, dev[0], dev[1], dev[2], dev[3])
                            : launch_init_t<float>(c, dev[0], dev[1], dev[2], dev[3]);
     if (e != hipSuccess) return hip_fail(e, "init kernel");
-    e = launch_mean_velocity(N, dev[0], dev[1], dev[2], c->scratch, kScratchDoubles, c->cnt,
-                             c->stream);
-    if (e != hipSuccess) return hip_fail(e, "mean velocity");
-    e = launch_frame_reach(N, dev[1], dev[2], dev[3], c->scratch, kScratchDoubles, c->cnt, c->stream);
-    if (e != hipSuccess) return hip_fail(e, "frame reach");
+    e = launch_field_sums(N, dev[0], dev[1], dev[2], dev[3], c->scratch, kScratchDoubles, c->cnt,
+                          c->stream);
+    if (e != hipSuccess) return hip_fail(e, "field sums");
     if (c->args.wall_h) {
         e = fp64(c) ? launch_ghost_check<double>(c->args, c->buf[0], c->cnt, c->stream)
                     : launch_ghost_check<float>(c->args, c->buf[0], c->cnt, c->stream);
@@ -565,10 +560,8 @@ pond_status pond_init_fields(pond_ctx *c, const double *rho, const double *ux, c
         return fail(POND_ERR_INVALID_ARG, "%llu nodes with rho <= 0, T <= 0 or non-finite values",
                     (unsigned long long)h.init_rejected);
     if (h.ghost_overrun) return ghost_band_refusal(c, h);
-    s = set_reference_from_counters(c);
+    s = set_reference(c, h);
     if (s == POND_OK) s = finish_init(c, h);
-    if (s != POND_OK) return s;
-    s = reset_counters(c);
     if (s != POND_OK) return s;
     c->steps = 0;
     c->initialized = true;
@@ -782,25 +775,21 @@ pond_status pond_import_state(pond_ctx *c, const double *f, const double *g, con
         if (e != hipSuccess) s = hip_fail(e, "import kernel");
     }
     if (s == POND_OK) {
-        if (u_ref) {
-            c->args.uref_x = u_ref[0];
-            c->args.uref_y = u_ref[1];
-        } else {
-            e = fp64(c) ? launch_state_mean_velocity<double>(c->args, c->buf[0], c->scratch,
-                                                             kScratchDoubles, c->cnt, c->stream)
-                        : launch_state_mean_velocity<float>(c->args, c->buf[0], c->scratch,
-                                                            kScratchDoubles, c->cnt, c->stream);
-            s = e == hipSuccess ? set_reference_from_counters(c) : hip_fail(e, "mean velocity");
-        }
-    }
-    if (s == POND_OK) {
-        e = launch_frame_reach(N, c->buf[0].ux, c->buf[0].uy, c->buf[0].T, c->scratch,
-                               kScratchDoubles, c->cnt, c->stream);
+        e = fp64(c) ? launch_state_sums<double>(c->args, c->buf[0], u_ref == nullptr, c->scratch,
+                                                kScratchDoubles, c->cnt, c->stream)
+                    : launch_state_sums<float>(c->args, c->buf[0], u_ref == nullptr, c->scratch,
+                                               kScratchDoubles, c->cnt, c->stream);
         if (e == hipSuccess && c->args.wall_h)
             e = fp64(c) ? launch_ghost_check<double>(c->args, c->buf[0], c->cnt, c->stream)
                         : launch_ghost_check<float>(c->args, c->buf[0], c->cnt, c->stream);
         DevCounters h;
-        s = e == hipSuccess ? read_counters(c, &h) : hip_fail(e, "frame reach");
+        s = e == hipSuccess ? read_counters(c, &h) : hip_fail(e, "state sums");
+        if (s == POND_OK && u_ref) {
+            c->args.uref_x = u_ref[0];
+            c->args.uref_y = u_ref[1];
+        } else if (s == POND_OK) {
+            s = set_reference(c, h);
+        }
         if (s == POND_OK && h.ghost_overrun) s = ghost_band_refusal(c, h);
         if (s == POND_OK) s = finish_init(c, h);
     }
@@ -808,8 +797,6 @@ pond_status pond_import_state(pond_ctx *c, const double *f, const double *g, con
         (void)hipStreamSynchronize(c->stream);
         (void)hipFree(tmp);
     }
-    if (s != POND_OK) return s;
-    s = reset_counters(c);
     if (s != POND_OK) return s;
     c->steps = 0;
     c->initialized = true;

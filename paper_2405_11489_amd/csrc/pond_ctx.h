@@ -38,7 +38,7 @@ struct Layout {
 // along trajectories from the last two levels; 0 otherwise.
 inline int prev_frame_planes(int split) { return split == POND_SPLIT_INTERNAL ? 2 : 0; }
 
-constexpr int kScratchDoubles = 3 * 256;
+constexpr int kScratchDoubles = 4 * 256;
 
 // Values of a node's moment groups (2 NM moments, padded): 20 on D2Q16; on
 // D2Q25 32 floats or 30 doubles.

@@ -178,17 +178,15 @@ hipError_t launch_export(const StepArgs &a, DevState st, double *f, double *g, d
 template <typename P>
 hipError_t launch_import(const StepArgs &a, const double *f, const double *g, const double *frame,
                          DevState st, hipStream_t s);
-// Deterministic mass-weighted mean velocity of (rho, ux, uy) into cnt->partial[0..2]
-// (sum rho, sum rho ux, sum rho uy), fixed summation order.
-hipError_t launch_mean_velocity(long long N, const double *rho, const double *ux, const double *uy,
-                                double *scratch, int scratch_len, DevCounters *cnt, hipStream_t s);
-// Largest stencil reach max(|u_x|, |u_y|) + c_out sqrt(T) over the nodes of a
-// frame, into cnt->partial[3].
-hipError_t launch_frame_reach(long long N, const double *ux, const double *uy, const double *T,
-                              double *scratch, int scratch_len, DevCounters *cnt, hipStream_t s);
-// Mass-weighted mean velocity of a stored state (populations + frame).
+// Of fields: the sums of rho, rho ux, rho uy (fixed summation order) into
+// cnt->partial[0..2] and the largest stencil reach max(|u_x|, |u_y|) + c_out sqrt(T)
+// into cnt->partial[3].
+hipError_t launch_field_sums(long long N, const double *rho, const double *ux, const double *uy,
+                             const double *T, double *scratch, int scratch_len, DevCounters *cnt,
+                             hipStream_t s);
+// The same of a stored state (populations + frame); without `mean` the reach alone.
 template <typename P>
-hipError_t launch_state_mean_velocity(const StepArgs &a, DevState st, double *scratch,
-                                      int scratch_len, DevCounters *cnt, hipStream_t s);
+hipError_t launch_state_sums(const StepArgs &a, DevState st, bool mean, double *scratch,
+                             int scratch_len, DevCounters *cnt, hipStream_t s);
 
 }  // namespace pond
