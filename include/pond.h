@@ -364,7 +364,8 @@ POND_API pond_status pond_step_noalloc(const pond_params *p, const double *u_ref
  * tile list), which also writes the moments of the state it produces; a
  * moment pre-pass over every member's nodes runs before it only when some
  * member's moments are stale (after pond_init_fields or pond_import_state).
- * Both launches are replayed from HIP graphs captured at creation.
+ * Batches with walled members, whose steps are several launches, replay them
+ * from HIP graphs captured at creation.
  *
  * Members must be D2Q16 contexts (POND_ERR_UNSUPPORTED otherwise; walls
  * included: their ghost rows are refilled after every batched step),
@@ -386,7 +387,7 @@ typedef struct {
     int32_t lds_nodes;    /* LDS capacity per block, in nodes */
     int64_t nodes;        /* nodes per batched step, all members */
     int64_t steps;        /* batched steps enqueued since creation */
-    int32_t graph_steps;  /* steps per launch of the larger captured graph */
+    int32_t graph_steps;  /* steps per captured graph (walled members) */
     int32_t reserved;
 } pond_batch_info_t;
 

@@ -272,15 +272,30 @@ void pond::fill_step_args(const pond_params &p, StepArgs &a) {
 
 namespace {
 
-bool is_device_pointer(const void *ptr) {
-    if (!ptr) return false;
+enum class Mem { kDevice, kPinned, kPageable };
+
+Mem memory_kind(const void *ptr) {
     hipPointerAttribute_t attr;
-    hipError_t e = hipPointerGetAttributes(&attr, ptr);
-    if (e != hipSuccess) {
+    if (hipPointerGetAttributes(&attr, ptr) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return Mem::kPageable;
     }
-    return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
+    if (attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged) return Mem::kDevice;
+    return attr.type == hipMemoryTypeUnregistered ? Mem::kPageable : Mem::kPinned;
+}
+
+bool is_device_pointer(const void *ptr) { return ptr && memory_kind(ptr) == Mem::kDevice; }
+
+// How many of the n planes of N doubles from planes[0] on one copy can take: those
+// that follow one another in pageable host memory.  (Planes in pinned memory may
+// be allocations that only happen to touch, which no copy may span.)
+template <typename T>
+int adjoining_planes(T *const *planes, int n, long long N) {
+    int k = 1;
+    while (k < n && planes[k] && planes[k] == planes[0] + k * N &&
+           memory_kind(planes[k - 1]) == Mem::kPageable && memory_kind(planes[k]) == Mem::kPageable)
+        ++k;
+    return k;
 }
 
 }  // namespace
@@ -526,14 +541,12 @@ pond_status pond_init_fields(pond_ctx *c, const double *rho, const double *ux, c
     double *stg = static_cast<double *>(c->mom[0]);
     const double *in[4] = {rho, ux, uy, T};
     const double *dev[4];
-    for (int k = 0; k < 4; ++k) {
-        if (is_device_pointer(in[k])) {
-            dev[k] = in[k];
-        } else {
-            s = stage_in(c, in[k], stg + k * N, N);
-            if (s != POND_OK) return s;
-            dev[k] = stg + k * N;
-        }
+    for (int k = 0; k < 4; ++k) dev[k] = is_device_pointer(in[k]) ? in[k] : stg + k * N;
+    for (int k = 0, n = 1; k < 4; k += n) {
+        n = dev[k] == in[k] ? 1 : adjoining_planes(in + k, 4 - k, N);
+        if (dev[k] == in[k]) continue;
+        s = stage_in(c, in[k], stg + k * N, n * N);
+        if (s != POND_OK) return s;
     }
     c->initialized = false;
     c->failed = false;
@@ -654,12 +667,13 @@ pond_status pond_moments(pond_ctx *c, double *rho, double *ux, double *uy, doubl
                            : launch_macro<float>(c->args, c->buf[c->cur], dev[0], dev[1], dev[2],
                                                  dev[3], dev[4], c->stream);
     if (e != hipSuccess) return hip_fail(e, "moments kernel");
-    for (int k = 0; k < 5; ++k)
-        if (outs[k] && dev[k] != outs[k]) {
-            e = hipMemcpyAsync(outs[k], dev[k], size_t(N) * sizeof(double), hipMemcpyDeviceToHost,
-                               c->stream);
-            if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(out)");
-        }
+    for (int k = 0, n = 1; k < 5; k += n) {
+        n = !outs[k] || dev[k] == outs[k] ? 1 : adjoining_planes(outs + k, 5 - k, N);
+        if (!outs[k] || dev[k] == outs[k]) continue;
+        e = hipMemcpyAsync(outs[k], dev[k], size_t(n) * N * sizeof(double), hipMemcpyDeviceToHost,
+                           c->stream);
+        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(out)");
+    }
     return sync_and_check(c);
 }
 

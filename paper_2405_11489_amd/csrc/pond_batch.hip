@@ -2,7 +2,7 @@
 // autotuner.
 //
 // A batch steps its member contexts with one launch per step for all of them
-// at once, replayed from captured HIP graphs: one step launch over the flat
+// at once: one step launch over the flat
 // list of every member's tiles, one block per tile; the hardware dispatcher
 // balances the tiles over the CUs, and the block -> tile map gives each XCD a
 // contiguous range of the list.  The step writes the moments the next step
@@ -10,8 +10,12 @@
 // belongs to one member) runs only where a member's moments are stale (after
 // its initialisation or an import).
 // Which of a member's two state buffers is current alternates every step;
-// the launches take that parity as an argument, so the batch keeps one graph
-// per starting parity and needs no device-side step counter.
+// the launches take that parity as an argument, so no device-side step counter
+// is needed.  Where members have walls a step is one launch more per such member;
+// those batches replay kGraphSteps steps from a captured HIP graph, one per
+// starting parity.  The others launch each step directly: a launch costs the host
+// 3.5 us, less than the smallest step takes, while the first launch of a graph
+// costs 40 us and its capture more, which a server pays at every regrouping.
 //
 // (A persistent variant -- a fixed grid pulling tiles from per-XCD atomic
 // queues -- ran 2.4x slower on one 512 x 512 instance: same-address
@@ -125,6 +129,25 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(
 #endif
 }
 
+// What pond_batch_synchronize reads of a member's counters.
+struct MemberFlags {
+    unsigned long long nonphysical, ghost_overrun;
+};
+
+// Block i: member i's flags, summed over its counter slots, for one copy to the
+// host instead of a copy and a wait per member.
+__global__ __launch_bounds__(kCounterSlots) void batch_flags_kernel(
+    const BatchMember *__restrict__ mem, MemberFlags *__restrict__ out) {
+    static_assert(kCounterSlots == 64, "one wave adds the slots");
+    const DevCounters *c = mem[blockIdx.x].cnt;
+    unsigned long long np = c->slot[threadIdx.x].nonphysical, go = c->slot[threadIdx.x].ghost_overrun;
+    for (int w = 32; w > 0; w >>= 1) {
+        np += __shfl_down(np, w);
+        go += __shfl_down(go, w);
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = MemberFlags{c->nonphysical + np, c->ghost_overrun + go};
+}
+
 template <typename P, int NP, int S, class L>
 const void *step_kernel_ptr() {
     return reinterpret_cast<const void *>(batch_step_kernel<P, NP, S, L>);
@@ -195,17 +218,20 @@ struct pond_batch {
     int np, split;
     hipStream_t stream;
     bool own_stream;
-    void *dev;  // [members | tile offsets | block offsets]
+    void *dev;  // [members | tile offsets | block offsets | flags]
     BatchMember *d_mem;
     int *d_tile_off, *d_blk_off;
+    MemberFlags *d_flags;
+    std::vector<MemberFlags> flags;  // as last read back
     int cap, tiles, blocks;
     int grid;     // blocks of the step launch
     int lattice;  // of every member
     long long nodes;
     long long steps;
-    // [parity][0]: one step, [parity][1]: kGraphSteps steps, starting at that parity
-    hipGraph_t graph[2][2];
-    hipGraphExec_t exec[2][2];
+    bool walled;  // a member has walls: a step is several launches
+    // walled batches: kGraphSteps steps, starting at that parity
+    hipGraph_t graph[2];
+    hipGraphExec_t exec[2];
     hipEvent_t done_ev;
     std::vector<hipStream_t> other_streams;  // member streams other than the batch's
     std::vector<hipEvent_t> other_ev;
@@ -283,11 +309,12 @@ hipError_t enqueue_batch_step(pond_batch *b, int flip) {
     return e == hipSuccess ? enqueue_batch_wall_ghosts(b, flip, 1) : e;
 }
 
-hipError_t capture(pond_batch *b, int steps, int flip, hipGraph_t *g, hipGraphExec_t *x) {
+hipError_t capture(pond_batch *b, int flip, hipGraph_t *g, hipGraphExec_t *x) {
     hipError_t e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
     hipError_t le = hipSuccess;
-    for (int k = 0; k < steps && le == hipSuccess; ++k) le = enqueue_batch_step(b, flip ^ (k & 1));
+    for (int k = 0; k < kGraphSteps && le == hipSuccess; ++k)
+        le = enqueue_batch_step(b, flip ^ (k & 1));
     e = hipStreamEndCapture(b->stream, g);
     if (le != hipSuccess) return le;
     if (e != hipSuccess) return e;
@@ -296,11 +323,10 @@ hipError_t capture(pond_batch *b, int steps, int flip, hipGraph_t *g, hipGraphEx
 
 void release(pond_batch *b) {
     if (b->stream) (void)hipStreamSynchronize(b->stream);
-    for (int f = 0; f < 2; ++f)
-        for (int k = 0; k < 2; ++k) {
-            if (b->exec[f][k]) (void)hipGraphExecDestroy(b->exec[f][k]);
-            if (b->graph[f][k]) (void)hipGraphDestroy(b->graph[f][k]);
-        }
+    for (int f = 0; f < 2; ++f) {
+        if (b->exec[f]) (void)hipGraphExecDestroy(b->exec[f]);
+        if (b->graph[f]) (void)hipGraphDestroy(b->graph[f]);
+    }
     if (b->done_ev) (void)hipEventDestroy(b->done_ev);
     for (hipEvent_t ev : b->other_ev) (void)hipEventDestroy(ev);
     if (b->dev) (void)hipFree(b->dev);
@@ -343,6 +369,7 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
     pond_batch *b = new (std::nothrow) pond_batch();
     if (!b) return fail(POND_ERR_OUT_OF_MEMORY, "host allocation failed");
     b->members.assign(ctxs, ctxs + n);
+    b->flags.resize(n);
     b->dbl = ctxs[0]->p.precision == POND_PREC_FP64;
     b->np = ctxs[0]->p.interp_points;
     b->split = ctxs[0]->p.split;
@@ -362,7 +389,7 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
     // LDS per block: the share of a CU of the blocks that fit by registers
     int per_cu = 0;
     const void *kern = batch_step_fn(b->dbl, b->np, b->split, b->lattice);
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBatchThreads, 0);
+    e = blocks_per_cu(kern, kBatchThreads, &per_cu);
     b->cap = lds_nodes_for_blocks(e == hipSuccess ? per_cu : 1, b->dbl, b->lattice);
     const size_t lds = size_t(b->cap) * lds_node_values(b->lattice, b->dbl) *
                        (b->dbl ? sizeof(double) : sizeof(float));
@@ -373,9 +400,14 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
         return hip_fail(e, "batch launch configuration");
     }
 
-    // descriptors
-    std::vector<BatchMember> hm(n);
-    std::vector<int> toff(n), boff(n);
+    // descriptors, laid out as on the device
+    const size_t mem_bytes = align_up(sizeof(BatchMember) * n);
+    const size_t off_bytes = align_up(sizeof(int) * n);
+    const size_t desc_bytes = mem_bytes + 2 * off_bytes;
+    std::vector<char> desc(desc_bytes);
+    BatchMember *hm = reinterpret_cast<BatchMember *>(desc.data());
+    int *toff = reinterpret_cast<int *>(desc.data() + mem_bytes);
+    int *boff = reinterpret_cast<int *>(desc.data() + mem_bytes + off_bytes);
     long long tiles = 0, blocks = 0, nodes = 0;
     for (int i = 0; i < n; ++i) {
         pond_ctx *c = ctxs[i];
@@ -387,7 +419,7 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
             return fail(POND_ERR_INVALID_ARG, "context %d: tile %dx%d does not fit %d LDS nodes", i,
                         w, h, b->cap);
         }
-        BatchMember &m = hm[i];
+        BatchMember &m = *new (hm + i) BatchMember;
         m.a = c->args;
         m.buf[0] = c->buf[0];
         m.buf[1] = c->buf[1];
@@ -405,6 +437,7 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
         tiles += (long long)tx * ty;
         blocks += (c->args.N + kBatchThreads - 1) / kBatchThreads;
         nodes += c->args.N;
+        b->walled = b->walled || c->args.wall_h > 0;
         b->widths.push_back(w);
     }
     if (tiles > 0x7fffffffll || blocks > 0x7fffffffll) {
@@ -425,9 +458,7 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
     b->blocks = int(blocks);
     b->nodes = nodes;
 
-    const size_t mem_bytes = align_up(sizeof(BatchMember) * n);
-    const size_t off_bytes = align_up(sizeof(int) * n);
-    e = hipMalloc(&b->dev, mem_bytes + 2 * off_bytes);
+    e = hipMalloc(&b->dev, desc_bytes + align_up(sizeof(MemberFlags) * n));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         b->dev = nullptr;
@@ -438,16 +469,13 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
     b->d_mem = reinterpret_cast<BatchMember *>(base);
     b->d_tile_off = reinterpret_cast<int *>(base + mem_bytes);
     b->d_blk_off = reinterpret_cast<int *>(base + mem_bytes + off_bytes);
+    b->d_flags = reinterpret_cast<MemberFlags *>(base + desc_bytes);
     // members' pending work (initialisation, earlier steps) precedes the batch's
     for (pond_ctx *c : b->members)
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e == hipSuccess) e = hipMemcpy(b->d_mem, hm.data(), sizeof(BatchMember) * n, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(b->d_tile_off, toff.data(), sizeof(int) * n, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(b->d_blk_off, boff.data(), sizeof(int) * n, hipMemcpyHostToDevice);
-    for (int f = 0; f < 2; ++f) {
-        if (e == hipSuccess) e = capture(b, 1, f, &b->graph[f][0], &b->exec[f][0]);
-        if (e == hipSuccess) e = capture(b, kGraphSteps, f, &b->graph[f][1], &b->exec[f][1]);
-    }
+    if (e == hipSuccess) e = hipMemcpy(b->dev, desc.data(), desc_bytes, hipMemcpyHostToDevice);
+    for (int f = 0; f < 2 && b->walled && e == hipSuccess; ++f)
+        e = capture(b, f, &b->graph[f], &b->exec[f]);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->done_ev, hipEventDisableTiming);
     for (pond_ctx *c : b->members) {
         if (e != hipSuccess) break;
@@ -491,10 +519,10 @@ pond_status pond_batch_step(pond_batch *b, int64_t nsteps) {
     bool stale = false;
     for (const pond_ctx *c : b->members) stale = stale || !c->mom_fresh;
     if (stale && e == hipSuccess) e = enqueue_batch_moments(b, f);
-    for (int64_t k = 0; k + kGraphSteps <= nsteps && e == hipSuccess; k += kGraphSteps)
-        e = hipGraphLaunch(b->exec[f][1], b->stream);
-    for (int64_t k = 0; k < nsteps % kGraphSteps && e == hipSuccess; ++k)
-        e = hipGraphLaunch(b->exec[f ^ int(k & 1)][0], b->stream);
+    int64_t k = 0;
+    for (; b->walled && k + kGraphSteps <= nsteps && e == hipSuccess; k += kGraphSteps)
+        e = hipGraphLaunch(b->exec[f], b->stream);
+    for (; k < nsteps && e == hipSuccess; ++k) e = enqueue_batch_step(b, f ^ int(k & 1));
     if (e == hipSuccess) e = hipEventRecord(b->done_ev, b->stream);
     for (size_t k = 0; k < b->other_streams.size() && e == hipSuccess; ++k)
         e = hipStreamWaitEvent(b->other_streams[k], b->done_ev, 0);
@@ -510,15 +538,29 @@ pond_status pond_batch_step(pond_batch *b, int64_t nsteps) {
 
 pond_status pond_batch_synchronize(pond_batch *b) {
     if (!b) return fail(POND_ERR_INVALID_ARG, "batch is NULL");
-    hipError_t e = hipStreamSynchronize(b->stream);
-    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+    // work of the members' own streams has ended too when this returns
+    for (hipStream_t s : b->other_streams) {
+        hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+    }
+    const size_t n = b->members.size();
+    hipLaunchKernelGGL(batch_flags_kernel, dim3(unsigned(n)), dim3(kCounterSlots), 0, b->stream,
+                       b->d_mem, b->d_flags);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b->flags.data(), b->d_flags, sizeof(MemberFlags) * n,
+                           hipMemcpyDeviceToHost, b->stream);
+    hipError_t e2 = hipStreamSynchronize(b->stream);
+    if (e == hipSuccess) e = e2;
+    if (e != hipSuccess) return hip_fail(e, "batch flags");
     int bad = 0;
     pond_status first = POND_OK;
-    for (pond_ctx *c : b->members) {
-        DevCounters h;
-        pond_status s = read_counters(c, &h);
-        if (s != POND_OK) return s;
-        s = counters_status(c, h);
+    for (size_t i = 0; i < n; ++i) {
+        pond_ctx *c = b->members[i];
+        DevCounters h{};
+        h.nonphysical = b->flags[i].nonphysical;
+        h.ghost_overrun = b->flags[i].ghost_overrun;
+        pond_status s = counters_status(c, h);
         if (s != POND_OK) {
             if (first == POND_OK) first = s;
             ++bad;

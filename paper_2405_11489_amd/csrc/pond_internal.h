@@ -112,6 +112,10 @@ inline bool quad_lanes(long long N, bool dbl) { return N <= (dbl ? 36864 : 49152
 // Blocks per CU of the four-lane kernels by registers (the LDS share of a block).
 inline int quad_blocks_per_cu(bool dbl) { return dbl ? 1 : 2; }
 
+// Blocks of a kernel per CU by registers and static LDS.  A property of the built
+// kernel, asked of the runtime once per kernel (a query takes some 10 us, and
+// contexts and batches are made per request).
+hipError_t blocks_per_cu(const void *kernel, int threads, int *out);
 // Blocks of the tiled step kernel (lattice, precision, stencil, energy split,
 // shape) that fit one CU by registers and waves alone (no dynamic LDS).
 int tiled_blocks_per_cu(int lattice, bool dbl, int np, int split, TileShape shape);

@@ -7,6 +7,9 @@
 // (FP32 mode: populations, moments, interpolation and frame transformation in
 // float; conserved sums, temperature recovery and the predictor-corrector test
 // in double).
+#include <map>
+#include <mutex>
+
 #include "pond_lattice_kernels.h"
 
 namespace pond {
@@ -124,6 +127,24 @@ hipError_t launch_step_tiled(const StepArgs &a, const TileConfig &tc, DevState s
                              DevState dst, P *mom_out, DevCounters *cnt, hipStream_t s) {
     return a.lattice == 25 ? Launch<P, D2Q25>::step_tiled(a, tc, src, mom, dst, mom_out, cnt, s)
                            : Launch<P, D2Q16>::step_tiled(a, tc, src, mom, dst, mom_out, cnt, s);
+}
+
+hipError_t blocks_per_cu(const void *kernel, int threads, int *out) {
+    static std::mutex mu;
+    static std::map<const void *, int> known;  // one entry per kernel of this library
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = known.find(kernel);
+    if (it != known.end()) {
+        *out = it->second;
+        return hipSuccess;
+    }
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(out, kernel, threads, 0);
+    if (e != hipSuccess) return e;
+    try {
+        known.emplace(kernel, *out);
+    } catch (...) {  // no memory to note it
+    }
+    return hipSuccess;
 }
 
 int tiled_blocks_per_cu(int lattice, bool dbl, int np, int split, TileShape shape) {

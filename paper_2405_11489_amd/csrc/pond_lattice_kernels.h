@@ -536,7 +536,7 @@ int Launch<P, L>::tiled_blocks_per_cu(int np, int split, TileShape shape) {
     int tx = 0, ty = 0;
     tile_dims(shape, tx, ty);
     int n = 0;
-    if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, tx * ty, 0) != hipSuccess) {
+    if (!k || blocks_per_cu(k, tx * ty, &n) != hipSuccess) {
         (void)hipGetLastError();
         return 1;
     }
