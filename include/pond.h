@@ -360,8 +360,8 @@ POND_API pond_status pond_step_noalloc(const pond_params *p, const double *u_ref
  * pond_step (the step of Sec. "Discrete velocity solver ...: PonD" with
  * Eq. propagationInterpolated; results are bit for bit those of pond_step on
  * the member alone).  One batched step is one step launch over the tiles of
- * every member (one block per tile, each XCD taking a contiguous range of the
- * tile list), which also writes the moments of the state it produces; a
+ * every member (one block per tile, every member's tiles split evenly over the
+ * XCDs), which also writes the moments of the state it produces; a
  * moment pre-pass over every member's nodes runs before it only when some
  * member's moments are stale (after pond_init_fields or pond_import_state).
  * Batches with walled members, whose steps are several launches, replay them
@@ -382,8 +382,7 @@ typedef struct pond_batch pond_batch; /* opaque */
 typedef struct {
     int32_t members;      /* contexts in the batch */
     int32_t tiles;        /* tiles per batched step, all members */
-    int32_t grid_blocks;  /* blocks of the step launch (one per tile; a build with
-                             POND_BATCH_PERSISTENT=1 launches a fixed grid) */
+    int32_t grid_blocks;  /* blocks of the step launch (one per tile and a few empty ones) */
     int32_t lds_nodes;    /* LDS capacity per block, in nodes */
     int64_t nodes;        /* nodes per batched step, all members */
     int64_t steps;        /* batched steps enqueued since creation */

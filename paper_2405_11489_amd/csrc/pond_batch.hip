@@ -2,13 +2,12 @@
 // autotuner.
 //
 // A batch steps its member contexts with one launch per step for all of them
-// at once: one step launch over the flat
-// list of every member's tiles, one block per tile; the hardware dispatcher
-// balances the tiles over the CUs, and the block -> tile map gives each XCD a
-// contiguous range of the list.  The step writes the moments the next step
-// reads; a flat moment pre-pass over every member's nodes (each 256-node block
-// belongs to one member) runs only where a member's moments are stale (after
-// its initialisation or an import).
+// at once, one block per tile of every member; the hardware dispatcher balances
+// the tiles over the CUs, and the block -> tile map splits every member evenly
+// over the XCDs.  The step writes the moments the next step reads; a flat moment
+// pre-pass over every member's nodes (each 256-node block belongs to one member)
+// runs only where a member's moments are stale (after its initialisation or an
+// import).
 // Which of a member's two state buffers is current alternates every step;
 // the launches take that parity as an argument, so no device-side step counter
 // is needed.  Where members have walls a step is one launch more per such member;
@@ -20,9 +19,9 @@
 // (A persistent variant -- a fixed grid pulling tiles from per-XCD atomic
 // queues -- ran 2.4x slower on one 512 x 512 instance: same-address
 // device-scope atomics serialise, and the cost grew with the grid.  A fixed
-// grid with static shares of the tile list and no atomics, the build option
-// POND_BATCH_PERSISTENT, ran a 256-instance mixed batch 4.6 % slower than the
-// flat launch: static shares do not follow the members' uneven tile costs.)
+// grid with static shares of the tile list and no atomics ran a 256-instance
+// mixed batch 4.6 % slower than the flat launch: static shares do not follow the
+// members' uneven tile costs.)
 //
 // Every node goes through the same per-node code as the single-instance
 // kernels (tile_step / node_step with the member's own arguments), so a
@@ -34,6 +33,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <tuple>
 #include <vector>
 
@@ -53,11 +53,20 @@ struct BatchMember {
     int parity0;   // current buffer of the member when the batch was built
     int lg;        // tile width 2^lg, height 256 >> lg
     int tiles_x;
-    int tile_off;  // first tile of the member in the flat tile list
+    int tiles;     // tiles of the member
+    int rot;       // its share k of the tiles (xcd_share) runs on XCD (k - rot) mod 8
     int blk_off;   // first pre-pass block of the member
 };
 
-// Largest i in [0, n) with off[i] <= v (off strictly increasing, off[0] = 0).
+constexpr int kXcds = 8;
+
+// First tile of share k of a member's tiles (share k ends where share k + 1 begins).
+__host__ __device__ constexpr int xcd_share(int tiles, int k) {
+    return int((long long)tiles * k / kXcds);
+}
+
+// Largest i in [0, n) with off[i] <= v (off nondecreasing, off[0] = 0, v < off[n]):
+// the member whose range holds v.
 __device__ __forceinline__ int find_member(const int *__restrict__ off, int n, int v) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
@@ -82,51 +91,32 @@ __global__ __launch_bounds__(kBatchThreads) void batch_moments_kernel(
     node_moments<P, L>(a, mem[i].buf[par], static_cast<P *>(mem[i].mom[par]), n);
 }
 
-// Tile t of the flat list: its member's step on that tile.
-template <typename P, int NP, int S, class L>
-__device__ __forceinline__ void batch_tile(const BatchMember *__restrict__ mem,
-                                           const int *__restrict__ tile_off, int nmem, int cap,
-                                           int flip, int t, unsigned char *smem_raw, int *red) {
-    const int i = __builtin_amdgcn_readfirstlane(find_member(tile_off, nmem, t));
-    const StepArgs a = mem[i].a;
-    const int lg = mem[i].lg, tiles_x = mem[i].tiles_x;
-    const int lt = t - mem[i].tile_off;
-    const int par = mem[i].parity0 ^ flip;
-    tile_step<P, NP, S, L>(a, mem[i].buf[par], static_cast<const P *>(mem[i].mom[par]),
-                               mem[i].buf[par ^ 1], static_cast<P *>(mem[i].mom[par ^ 1]),
-                     mem[i].cnt, reinterpret_cast<P *>(smem_raw), cap, (lt % tiles_x) << lg,
-                     (lt / tiles_x) * (kBatchThreads >> lg), Shape256{lg}, red);
-}
-
-// POND_BATCH_PERSISTENT=1: a fixed grid of the blocks the chip holds at once,
-// block b (on XCD b % 8) stepping, in turn, a static share of its XCD's
-// contiguous range of the tile list (no queue, no atomics).  Off by default
-// (slower; see the note at the top of this file).
-#ifndef POND_BATCH_PERSISTENT
-#define POND_BATCH_PERSISTENT 0
-#endif
-
+// Block b runs on XCD b % 8 and takes that XCD's tile b / 8.  Every member's tiles
+// are split evenly over the XCDs, each taking a contiguous share (whose source
+// regions overlap in its L2), members of long stencil reach -- the ones that cost
+// most per tile -- first.  With the members one after another over the whole list
+// an XCD could hold nothing but the cheap ones: a mixed batch of 24 instances took
+// 320 us per step that way and takes 289 us this way.
+// xcd_off: per XCD x the offsets [x (nmem + 1) + i] of member i's tiles in its list.
 template <typename P, int NP, int S, class L>
 __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(
     step_min_waves<P, S, kBatchThreads, L>()))) void batch_step_kernel(
-    const BatchMember *__restrict__ mem, const int *__restrict__ tile_off, int nmem, int cap,
-    int flip, int ntiles) {
+    const BatchMember *__restrict__ mem, const int *__restrict__ xcd_off, int nmem, int cap,
+    int flip) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ int red[bound_slots<Shape256::kThreads>()];
-#if POND_BATCH_PERSISTENT
-    // the grid has at least 8 blocks, so every XCD has one
-    const int b = int(blockIdx.x), nb = int(gridDim.x), x = b % 8;
-    const int on_xcd = (nb - x + 7) / 8;
-    const int lo = int((long long)x * ntiles / 8), hi = int((long long)(x + 1) * ntiles / 8);
-    for (int t = lo + b / 8; t < hi; t += on_xcd) {
-        batch_tile<P, NP, S, L>(mem, tile_off, nmem, cap, flip, t, smem_raw, red);
-        __syncthreads();  // the next tile's staging overwrites the LDS
-    }
-#else
-    (void)ntiles;
-    batch_tile<P, NP, S, L>(mem, tile_off, nmem, cap, flip,
-                            xcd_tile(int(blockIdx.x), int(gridDim.x)), smem_raw, red);
-#endif
+    const int xcd = int(blockIdx.x) % kXcds, j = int(blockIdx.x) / kXcds;
+    const int *off = xcd_off + xcd * (nmem + 1);
+    if (j >= off[nmem]) return;
+    const int i = __builtin_amdgcn_readfirstlane(find_member(off, nmem, j));
+    const StepArgs a = mem[i].a;
+    const int lg = mem[i].lg, tiles_x = mem[i].tiles_x;
+    const int lt = xcd_share(mem[i].tiles, (xcd + mem[i].rot) % kXcds) + j - off[i];
+    const int par = mem[i].parity0 ^ flip;
+    tile_step<P, NP, S, L>(a, mem[i].buf[par], static_cast<const P *>(mem[i].mom[par]),
+                           mem[i].buf[par ^ 1], static_cast<P *>(mem[i].mom[par ^ 1]), mem[i].cnt,
+                           reinterpret_cast<P *>(smem_raw), cap, (lt % tiles_x) << lg,
+                           (lt / tiles_x) * (kBatchThreads >> lg), Shape256{lg}, red);
 }
 
 // What pond_batch_synchronize reads of a member's counters.
@@ -218,9 +208,10 @@ struct pond_batch {
     int np, split;
     hipStream_t stream;
     bool own_stream;
-    void *dev;  // [members | tile offsets | block offsets | flags]
+    std::vector<int> order;    // the member at each place of the device tables
+    void *dev;  // [members | tile offsets per XCD | block offsets | flags]
     BatchMember *d_mem;
-    int *d_tile_off, *d_blk_off;
+    int *d_xcd_off, *d_blk_off;
     MemberFlags *d_flags;
     std::vector<MemberFlags> flags;  // as last read back
     int cap, tiles, blocks;
@@ -289,12 +280,12 @@ void launch_batch_step(pond_batch *b, int flip) {
     with_variant(b->np, b->split, [&](auto np, auto sp) {
         if (b->dbl)
             hipLaunchKernelGGL((batch_step_kernel<double, np(), sp(), L>), dim3(b->grid),
-                               dim3(kBatchThreads), lds, b->stream, b->d_mem, b->d_tile_off, n,
-                               b->cap, flip, b->tiles);
+                               dim3(kBatchThreads), lds, b->stream, b->d_mem, b->d_xcd_off, n,
+                               b->cap, flip);
         else
             hipLaunchKernelGGL((batch_step_kernel<float, np(), sp(), L>), dim3(b->grid),
-                               dim3(kBatchThreads), lds, b->stream, b->d_mem, b->d_tile_off, n,
-                               b->cap, flip, b->tiles);
+                               dim3(kBatchThreads), lds, b->stream, b->d_mem, b->d_xcd_off, n,
+                               b->cap, flip);
         return 0;
     });
 }
@@ -402,14 +393,21 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
 
     // descriptors, laid out as on the device
     const size_t mem_bytes = align_up(sizeof(BatchMember) * n);
-    const size_t off_bytes = align_up(sizeof(int) * n);
-    const size_t desc_bytes = mem_bytes + 2 * off_bytes;
+    const size_t xcd_bytes = align_up(sizeof(int) * kXcds * (size_t(n) + 1));
+    const size_t desc_bytes = mem_bytes + xcd_bytes + align_up(sizeof(int) * n);
     std::vector<char> desc(desc_bytes);
     BatchMember *hm = reinterpret_cast<BatchMember *>(desc.data());
-    int *toff = reinterpret_cast<int *>(desc.data() + mem_bytes);
-    int *boff = reinterpret_cast<int *>(desc.data() + mem_bytes + off_bytes);
+    int *xoff = reinterpret_cast<int *>(desc.data() + mem_bytes);
+    int *boff = reinterpret_cast<int *>(desc.data() + mem_bytes + xcd_bytes);
+    b->parity0.resize(n);
+    b->widths.resize(n);
+    b->order.resize(n);
+    std::iota(b->order.begin(), b->order.end(), 0);
+    std::stable_sort(b->order.begin(), b->order.end(),
+                     [&](int i, int j) { return ctxs[i]->reach > ctxs[j]->reach; });
     long long tiles = 0, blocks = 0, nodes = 0;
-    for (int i = 0; i < n; ++i) {
+    for (int k = 0; k < n; ++k) {
+        const int i = b->order[k];
         pond_ctx *c = ctxs[i];
         const int w = member_width(c), lg = lg2(w), h = kBatchThreads >> lg;
         const int tx = (c->p.nx + w - 1) / w, ty = (c->p.ny + h - 1) / h;
@@ -419,7 +417,7 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
             return fail(POND_ERR_INVALID_ARG, "context %d: tile %dx%d does not fit %d LDS nodes", i,
                         w, h, b->cap);
         }
-        BatchMember &m = *new (hm + i) BatchMember;
+        BatchMember &m = *new (hm + k) BatchMember;
         m.a = c->args;
         m.buf[0] = c->buf[0];
         m.buf[1] = c->buf[1];
@@ -427,34 +425,31 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
         m.mom[1] = c->mom[1];
         m.cnt = c->cnt;
         m.parity0 = c->cur;
-        b->parity0.push_back(c->cur);
+        b->parity0[i] = c->cur;
         m.lg = lg;
         m.tiles_x = tx;
-        m.tile_off = int(tiles);
+        m.tiles = tx * ty;
+        m.rot = int(tiles % kXcds);  // the larger shares of the members spread over the XCDs
         m.blk_off = int(blocks);
-        toff[i] = int(tiles);
-        boff[i] = int(blocks);
+        boff[k] = int(blocks);
+        for (int x = 0; x < kXcds; ++x) {
+            const int share = (x + m.rot) % kXcds;
+            int *off = xoff + x * (n + 1) + k;
+            off[1] = off[0] + xcd_share(m.tiles, share + 1) - xcd_share(m.tiles, share);
+        }
         tiles += (long long)tx * ty;
         blocks += (c->args.N + kBatchThreads - 1) / kBatchThreads;
         nodes += c->args.N;
         b->walled = b->walled || c->args.wall_h > 0;
-        b->widths.push_back(w);
+        b->widths[i] = w;
     }
     if (tiles > 0x7fffffffll || blocks > 0x7fffffffll) {
         release(b);
         return fail(POND_ERR_INVALID_ARG, "batch too large (%lld tiles)", tiles);
     }
     b->tiles = int(tiles);
-    b->grid = b->tiles;
-    if (POND_BATCH_PERSISTENT) {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            per_cu > 0 && cus > 0)
-            b->grid = std::max(8, (per_cu * cus + 7) / 8 * 8);
-        else
-            b->grid = std::max(8, b->tiles);
-    }
+    b->grid = 0;
+    for (int x = 0; x < kXcds; ++x) b->grid = std::max(b->grid, kXcds * xoff[x * (n + 1) + n]);
     b->blocks = int(blocks);
     b->nodes = nodes;
 
@@ -467,8 +462,8 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
     }
     char *base = static_cast<char *>(b->dev);
     b->d_mem = reinterpret_cast<BatchMember *>(base);
-    b->d_tile_off = reinterpret_cast<int *>(base + mem_bytes);
-    b->d_blk_off = reinterpret_cast<int *>(base + mem_bytes + off_bytes);
+    b->d_xcd_off = reinterpret_cast<int *>(base + mem_bytes);
+    b->d_blk_off = reinterpret_cast<int *>(base + mem_bytes + xcd_bytes);
     b->d_flags = reinterpret_cast<MemberFlags *>(base + desc_bytes);
     // members' pending work (initialisation, earlier steps) precedes the batch's
     for (pond_ctx *c : b->members)
@@ -556,7 +551,7 @@ pond_status pond_batch_synchronize(pond_batch *b) {
     int bad = 0;
     pond_status first = POND_OK;
     for (size_t i = 0; i < n; ++i) {
-        pond_ctx *c = b->members[i];
+        pond_ctx *c = b->members[b->order[i]];
         DevCounters h{};
         h.nonphysical = b->flags[i].nonphysical;
         h.ghost_overrun = b->flags[i].ghost_overrun;
