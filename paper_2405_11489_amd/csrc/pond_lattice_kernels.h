@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kBlock) void step_kernel(StepArgs a, DevState src,
     }
     GlobalTaps<P, NP, L> taps{mom, a.mstride, a.nx, a.ny, a.bc_x, a.bc_y, a.moff, a.wall_h, {}};
     taps.set_reference(x, y);
-    node_step<P, NP, S, L, false>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
+    node_step<P, NP, S, L, NodeLanes::kOne>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
 }
 
 // ------------------------------------------------------ step (LDS tiles) ----

@@ -317,7 +317,10 @@ struct GlobalTaps {
     __device__ __forceinline__ Row staged(int, int) const { return Row{}; }
 };
 
-// Four lanes per node (Quad kernels): lane j of a group of four holds x-component
+// How many lanes gather a node (node_step).
+enum class NodeLanes { kOne, kRegroup, kFour };
+
+// Four lanes per node: lane j of a group of four holds x-component
 // j's share.  quad_lane(v, j): the value of the group's lane j.
 template <int J>
 __device__ __forceinline__ int quad_lane(int v) {
@@ -330,6 +333,19 @@ __device__ __forceinline__ float quad_lane(float v) {
 template <int J>
 __device__ __forceinline__ double quad_lane(double v) {
     return __hiloint2double(quad_lane<J>(__double2hiint(v)), quad_lane<J>(__double2loint(v)));
+}
+
+// Position of the k-th set bit of mask (k = 0 the lowest), which has more than k.
+__device__ __forceinline__ int nth_set_bit(unsigned long long mask, int k) {
+    int pos = 0;
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) {
+        const int c = __popcll((mask >> pos) & ((1ull << w) - 1));
+        const bool up = k >= c;
+        k -= up ? c : 0;
+        pos += up ? w : 0;
+    }
+    return pos;
 }
 
 // Lanes of the wave for which c holds (a ballot and a scalar bit count).
@@ -536,12 +552,19 @@ namespace pond {
 // lab moments follow once, from the last gather's) are accumulated on the fly,
 // so no population array is kept.
 //
-// Quad: four lanes share the node (every argument alike), one per x-component:
+// NodeLanes::kFour: four lanes share the node (every argument alike), one per x-component:
 // each gathers and reconstructs its own x-component, and the sums over the
 // x-components are formed by every lane, in the order of the loop over them, so
 // the bits are those of one lane per node.  Small grids, whose few waves leave
 // most of the chip idle, take a quarter of the gather's time per step this way.
-template <typename P, int NP, int S, class L, bool Quad, class Taps>
+//
+// kRegroup: one lane per node, but once at most 16 of a wave's nodes are left to
+// converge, they are gathered the same way, four lanes each (the wave's nodes must
+// share their reference node).  Near shocks most waves iterate for a few nodes only
+// (a 308^2 shock tube: 0.6 of 1.8 gathers per wave and step), and the launch ends
+// with the wave of the most iterations: 0.100 / 0.065 ms per step of that tube
+// without / with, 0.237 / 0.191 of the 613 x 377 quadrants in FP64.
+template <typename P, int NP, int S, class L, NodeLanes Lanes, class Taps>
 __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, int x, int y,
                                           long long n, bool live, double l0, double l1, double l2,
                                           const DevState &src, DevState dst,
@@ -551,13 +574,14 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
     double lg0 = l0, lg1 = l1, lg2 = l2;     // frame of the current gather
     double ln0 = lg0, ln1 = lg1, ln2 = lg2;  // frame of the gathered moments
     double rho = 1.0, gsum = 0.0;  // FP64 sums of the last gather's f and g
-    P Mf[NM], Mg[NM];  // lab moments (about u_ref) of the last gather's populations
-    P Cf[NM], Cg[NM];  // their lattice sums (column_add), in the gather's frame
+    P Cf[NM], Cg[NM];  // lattice sums of the last gather's populations, in its frame
 #pragma unroll
-    for (int k = 0; k < NM; ++k) Mf[k] = Mg[k] = Cf[k] = Cg[k] = P(0);
+    for (int k = 0; k < NM; ++k) Cf[k] = Cg[k] = P(0);
     bool done = !live, conv = false, bad = false, overrun = false;
+    constexpr bool Quad = Lanes == NodeLanes::kFour;
     const int quad = Quad ? int(threadIdx.x) & 3 : 0;
     const bool owner = quad == 0;  // the lane that counts its node
+    constexpr bool kRegroup = Lanes == NodeLanes::kRegroup;
     unsigned long long itc = 0;  // gathers of the wave's lanes
     // internal split: the source's velocity gradient (the same for every
     // iterate), in the arithmetic's precision
@@ -573,93 +597,135 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
         }
     }
 
-    // lab moments of a gather's populations from its lattice sums (frame scale sP,
+    // lab moments of a gather's populations from their lattice sums C (frame scale sP,
     // offset (dux, duy) from u_ref); where the gather sums the deviations from the
-    // reference moments, their share is added here
-    auto lab_moments = [&](P sP, P dux, P duy) {
-        moments_from_lattice_sums<L>(Cf, sP, dux, duy, Mf);
-        moments_from_lattice_sums<L>(Cg, sP, dux, duy, Mg);
+    // reference moments, their share is added here (first: its place among them)
+    auto lab_moments = [&](const P (&C)[NM], int first, P sP, P dux, P duy, P (&M)[NM]) {
+        moments_from_lattice_sums<L>(C, sP, dux, duy, M);
         if constexpr (deviations<P>()) {
 #pragma unroll
-            for (int k = 0; k < NM; ++k) {
-                Mf[k] += taps.ref_at(k);
-                Mg[k] += taps.ref_at(NM + k);
-            }
+            for (int k = 0; k < NM; ++k) M[k] += taps.ref_at(first + k);
         }
     };
 
+    struct Sums {
+        double sr, r, mx, my, m2, Eg;
+    };
+    // The gather of node (gx, gy) in the frame (g0, g1, g2): the FP64 sums and the
+    // lattice sums of its populations.  four: by a group of four lanes (see above).
+    auto gather = [&](auto four, int gx, int gy, double g0, double g1, double g2, Sums &o,
+                      P (&Of)[NM], P (&Og)[NM]) {
+        constexpr bool kFour = decltype(four)::value;
+        double s, isd;
+        frame_scale(g2, s, isd);
+        const P dux = P(g0 - a.uref_x), duy = P(g1 - a.uref_y), is = P(isd);
+        const double sr = rounded_scale(s, is);
+        // departure coordinates x - (s c + u) = (x - u) - s c, from the iterate
+        // frame clamped to a finite range (a non-physical iterate, which the
+        // test below flags, must still index inside the grid)
+        const double sc = fmin(fmax(s, 0.0), 1.0e6);
+        const double xu = double(gx) - fmin(fmax(g0, -1.0e8), 1.0e8);
+        const double yu = double(gy) - fmin(fmax(g1, -1.0e8), 1.0e8);
+        o = Sums{sr, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < NM; ++k) Of[k] = Og[k] = P(0);
+        // x-component ia's populations gathered in the iterate frame, over their
+        // weights: the FP64 sums of f, f c and g (and f |c|^2), and the lattice sums
+        auto add = [&](int ia, double s0, double s1, double s2, double sg,
+                       const P (&Sf)[L::N + 1], const P (&Sg)[L::N + 1]) {
+            const double ca = L::c(ia), wa = gather_weight<P, L>(ia);
+            s0 *= wa;
+            o.r += s0;
+            o.mx += ca * s0;
+            o.my += wa * s1;
+            if constexpr (S == 2) o.m2 += ca * ca * s0 + wa * s2;
+            o.Eg += wa * sg;
+            column_flush<L, true>(Of, Sf, ia);
+            column_flush<L, true>(Og, Sg, ia);
+        };
+        auto column = [&](int ia, const P (&f)[L::Q1], const P (&g)[L::Q1]) {
+            double s0 = 0.0, s1 = 0.0, s2 = 0.0, sg = 0.0;
+#pragma unroll
+            for (int b = 0; b < L::Q1; ++b) {
+                const double fd = double(f[b]), cb = L::c(b);
+                const double wb = gather_weight<P, L>(b);
+                s0 += wb * fd;
+                if (cb != 0.0) s1 += (wb * cb) * fd;
+                if constexpr (S == 2) s2 += (wb * cb * cb) * fd;
+                sg += wb * double(g[b]);
+            }
+            P Sf[L::N + 1], Sg[L::N + 1];
+            column_sums<L, true>(f, Sf);
+            column_sums<L, true>(g, Sg);
+            if constexpr (kFour) {
+                auto from = [&](auto lane) {
+                    constexpr int J = decltype(lane)::value;
+                    P Tf[L::N + 1], Tg[L::N + 1];
+#pragma unroll
+                    for (int q = 0; q <= L::N; ++q) {
+                        Tf[q] = quad_lane<J>(Sf[q]);
+                        Tg[q] = quad_lane<J>(Sg[q]);
+                    }
+                    add(J, quad_lane<J>(s0), quad_lane<J>(s1),
+                        S == 2 ? quad_lane<J>(s2) : 0.0, quad_lane<J>(sg), Tf, Tg);
+                };
+                from(std::integral_constant<int, 0>{});
+                from(std::integral_constant<int, 1>{});
+                from(std::integral_constant<int, 2>{});
+                from(std::integral_constant<int, 3>{});
+            } else {
+                add(ia, s0, s1, s2, sg, Sf, Sg);
+            }
+        };
+        gather_rows<P, NP, L, kFour>(taps, xu, yu, sc, dux, duy, is, P(sr * sr), column);
+    };
+
     for (int it = 0; it < a.pc_max_iter; ++it) {
-        itc += wave_count(!done && owner);
+        const unsigned long long open = __ballot(!done);
+        itc += (unsigned long long)__popcll(open) / (Quad ? 4 : 1);
+        Sums o{};
+        if (!kRegroup || __popcll(open) > 16) {
+            if (!done)
+                gather(std::integral_constant<bool, Quad>{}, x, y, lg0, lg1, lg2, o, Cf, Cg);
+        } else if constexpr (kRegroup) {
+            // a few nodes are left: four lanes for each, whether their own nodes are
+            // done or not; group k takes the k-th node left
+            const int k = (int(threadIdx.x) & 63) >> 2;
+            const bool mine = k < __popcll(open);
+            const int from = nth_set_bit(open, mine ? k : 0);
+            Sums q{};
+            P Kf[NM], Kg[NM];
+            const int gx = __shfl(x, from), gy = __shfl(y, from);
+            const double g0 = __shfl(lg0, from), g1 = __shfl(lg1, from), g2 = __shfl(lg2, from);
+            if (mine) gather(std::true_type{}, gx, gy, g0, g1, g2, q, Kf, Kg);
+            const int group = 4 * __popcll(open & ((1ull << (threadIdx.x & 63)) - 1));
+            const int at = done ? 0 : group;
+            o.sr = __shfl(q.sr, at);
+            o.r = __shfl(q.r, at);
+            o.mx = __shfl(q.mx, at);
+            o.my = __shfl(q.my, at);
+            if constexpr (S == 2) o.m2 = __shfl(q.m2, at);
+            o.Eg = __shfl(q.Eg, at);
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {
+                const P f = __shfl(Kf[i], at), g = __shfl(Kg[i], at);
+                if (!done) {
+                    Cf[i] = f;
+                    Cg[i] = g;
+                }
+            }
+        }
         if (!done) {
-            double s, isd;
-            frame_scale(lg2, s, isd);
             if (a.bc_y == 2) {
                 // walls: every stencil row must lie within the ghost rows
+                double s, isd;
+                frame_scale(lg2, s, isd);
                 int lo, hi;
                 stencil_extent<NP, L>(y, lg1, s, lo, hi);
                 if (lo < -a.wall_h || hi > a.ny - 1 + a.wall_h) overrun = true;
             }
-            const P dux = P(lg0 - a.uref_x), duy = P(lg1 - a.uref_y), is = P(isd);
-            const double sr = rounded_scale(s, is);
-            const P sP = P(sr);
-            // departure coordinates x - (s c + u) = (x - u) - s c, from the iterate
-            // frame clamped to a finite range (a non-physical iterate, which the
-            // test below flags, must still index inside the grid)
-            const double sc = fmin(fmax(s, 0.0), 1.0e6);
-            const double xu = double(x) - fmin(fmax(lg0, -1.0e8), 1.0e8);
-            const double yu = double(y) - fmin(fmax(lg1, -1.0e8), 1.0e8);
-            double r = 0.0, mx = 0.0, my = 0.0, m2 = 0.0, Eg = 0.0;
-#pragma unroll
-            for (int k = 0; k < NM; ++k) Cf[k] = Cg[k] = P(0);
-            // x-component ia's populations gathered in the iterate frame, over their
-            // weights: the FP64 sums of f, f c and g (and f |c|^2), and the lattice sums
-            auto add = [&](int ia, double s0, double s1, double s2, double sg,
-                           const P (&Sf)[L::N + 1], const P (&Sg)[L::N + 1]) {
-                const double ca = L::c(ia), wa = gather_weight<P, L>(ia);
-                s0 *= wa;
-                r += s0;
-                mx += ca * s0;
-                my += wa * s1;
-                if constexpr (S == 2) m2 += ca * ca * s0 + wa * s2;
-                Eg += wa * sg;
-                column_flush<L, true>(Cf, Sf, ia);
-                column_flush<L, true>(Cg, Sg, ia);
-            };
-            auto column = [&](int ia, const P (&f)[L::Q1], const P (&g)[L::Q1]) {
-                double s0 = 0.0, s1 = 0.0, s2 = 0.0, sg = 0.0;
-#pragma unroll
-                for (int b = 0; b < L::Q1; ++b) {
-                    const double fd = double(f[b]), cb = L::c(b);
-                    const double wb = gather_weight<P, L>(b);
-                    s0 += wb * fd;
-                    if (cb != 0.0) s1 += (wb * cb) * fd;
-                    if constexpr (S == 2) s2 += (wb * cb * cb) * fd;
-                    sg += wb * double(g[b]);
-                }
-                P Sf[L::N + 1], Sg[L::N + 1];
-                column_sums<L, true>(f, Sf);
-                column_sums<L, true>(g, Sg);
-                if constexpr (Quad) {
-                    auto from = [&](auto lane) {
-                        constexpr int J = decltype(lane)::value;
-                        P Tf[L::N + 1], Tg[L::N + 1];
-#pragma unroll
-                        for (int q = 0; q <= L::N; ++q) {
-                            Tf[q] = quad_lane<J>(Sf[q]);
-                            Tg[q] = quad_lane<J>(Sg[q]);
-                        }
-                        add(J, quad_lane<J>(s0), quad_lane<J>(s1),
-                            S == 2 ? quad_lane<J>(s2) : 0.0, quad_lane<J>(sg), Tf, Tg);
-                    };
-                    from(std::integral_constant<int, 0>{});
-                    from(std::integral_constant<int, 1>{});
-                    from(std::integral_constant<int, 2>{});
-                    from(std::integral_constant<int, 3>{});
-                } else {
-                    add(ia, s0, s1, s2, sg, Sf, Sg);
-                }
-            };
-            gather_rows<P, NP, L, Quad>(taps, xu, yu, sc, dux, duy, is, P(sr * sr), column);
+            const double sr = o.sr, mx = o.mx, my = o.my, m2 = o.m2;
+            double r = o.r, Eg = o.Eg;
             // momentum, and in the non-translational split the energy f carries, at
             // the velocities C = s c + u of the iterate frame
             double jx = sr * mx + lg0 * r, jy = sr * my + lg1 * r, E = Eg;
@@ -692,12 +758,13 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
 
             // total split: sum g = E = rho c_v T + |j|^2 / (2 rho); internal: sum g = rho c_v T;
             // non-translational: E = sum g + sum f |C|^2 / 2 = rho c_v T + |j|^2 / (2 rho)
-            if constexpr (S == 1) lab_moments(sP, dux, duy);
             if constexpr (S == 1) {
                 // the energy of the step's middle, U = sum g + (sum G) / 2, with the
                 // source's sum G = -(omega / 2) rho T div u - (1 - omega / 2) P : grad u
                 // (P the pressure tensor of the gathered f about u, from its moments
                 // about u_ref): rho c_v T = U solved for T
+                P Mf[NM];
+                lab_moments(Cf, 0, P(sr), P(lg0 - a.uref_x), P(lg1 - a.uref_y), Mf);
                 const double dx = ln0 - a.uref_x, dy = ln1 - a.uref_y;
                 const double m00 = double(Mf[mom_index(0, 0)]), m10 = double(Mf[mom_index(1, 0)]);
                 const double m01 = double(Mf[mom_index(0, 1)]), m20 = double(Mf[mom_index(2, 0)]);
@@ -739,11 +806,15 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
     }
 
     if (live) {
-        if constexpr (S != 1) {
+        P Mf[NM], Mg[NM];  // about u_ref
+        {
             // the last gather's frame (lam is only advanced when another gather follows)
             double s, isd;
             frame_scale(lg2, s, isd);
-            lab_moments(P(rounded_scale(s, P(isd))), P(lg0 - a.uref_x), P(lg1 - a.uref_y));
+            const P sP = P(rounded_scale(s, P(isd)));
+            const P dux = P(lg0 - a.uref_x), duy = P(lg1 - a.uref_y);
+            lab_moments(Cf, 0, sP, dux, duy, Mf);
+            lab_moments(Cg, NM, sP, dux, duy, Mg);
         }
         // re-projection onto lam* = (ln0, ln1, ln2): Grad coefficients there
         double sT, isT;

@@ -314,7 +314,13 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, DevState src, const
     __syncthreads();
 
     const TileTaps<P, NP, L> taps{lds, cap, X0, Y0, X1, Y1, W, glob};
-    node_step<P, NP, S, L, Quad>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
+    // regrouping costs registers, which FP64 blocks of 512 lanes lack (256 per lane:
+    // 0.36 against 0.29 ms per step of 512^2, Mach 2)
+    constexpr NodeLanes kNodeLanes =
+        Quad ? NodeLanes::kFour
+        : L::Q1 == 4 && (sizeof(P) == 4 || Shape::kThreads <= 256) ? NodeLanes::kRegroup
+                                                                   : NodeLanes::kOne;
+    node_step<P, NP, S, L, kNodeLanes>(a, taps, x, y, n, live, l0, l1, l2, src, dst, mom_out, cnt);
 }
 
 // Moments up to the lattice's Grad order (three on D2Q16, four on D2Q25) of
