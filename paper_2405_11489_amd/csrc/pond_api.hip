@@ -138,16 +138,13 @@ static long long tiles_of(const pond_params &p, int tx, int ty) {
 }
 
 // Block shape: 64 x 1 rows for (quasi-)one-dimensional grids, else 32 x 8.
-// D2Q16 takes the 512-lane 32 x 16 tile in FP64 when its tiles cover every CU
-// (one block per CU holds the whole LDS, as one 32 x 8 block does, with twice
-// the waves: 717 against 545 MLUPS at 512^2, Mach 2, 718 against 562 at
-// 1024^2, 1157 against 864 on the 2048^2 quadrants; at 256^2 its 128 tiles
-// leave half the CUs idle: 376 against 479), and in FP32 when the grid needs
-// more than one round of 32 x 8 blocks but fits one round of 32 x 16 blocks (a
-// kernel that runs more waves per SIMD with 512-lane blocks than with 256-lane
-// ones).  The FP32 D2Q16 kernels with the shared x-pass run two waves per SIMD
-// at either block size, so they keep 32 x 8 (2048^2 quadrants: 1.13 against
-// 1.32 ms per step with 32 x 16; 512^2 Mach 2: 0.153 against 0.159 ms).
+// D2Q16 takes the 512-lane 32 x 16 tile in FP64 when its tiles cover every CU (one
+// block per CU holds the whole LDS; 512^2, Mach 2: 0.29 ms per step against 0.34
+// with 32 x 8; at 256^2 its 128 tiles leave half the CUs idle: 0.132 against 0.085),
+// and in FP32 when the grid needs more than one round of 32 x 8 blocks but fits one
+// round of 32 x 16 blocks (a kernel that runs more waves per SIMD with 512-lane
+// blocks than with 256-lane ones; two either way as built, so it keeps 32 x 8:
+// 2048^2 quadrants 0.81 against 0.85 ms, 512^2 Mach 2 0.113 against 0.114).
 pond_tuning default_tuning(const pond_params &p, int reach) {
     pond_tuning t;
     t.kernel = POND_KERNEL_TILED;
@@ -175,7 +172,7 @@ pond_tuning default_tuning(const pond_params &p, int reach) {
     // flows whose stencils reach two nodes at most (cold, slow): small tiles, which
     // carry little more halo there and end their waves sooner where the
     // predictor-corrector work varies (2048^2 quadrants, FP32: 0.70 ms per step
-    // against 0.80 with 32 x 8; 1024^2, FP64: 0.58 against 0.69)
+    // against 0.81 with 32 x 8; 1024^2, FP64: 0.55 against 0.62)
     const bool small = reach > 0 && reach <= 2 && p.ny >= 16;
     // D2Q25: square tiles, whose source regions carry less halo per node (512^2
     // Mach 2: 545 against 495 MLUPS with 32 x 8)
