@@ -71,8 +71,9 @@ CANON_BYTES_FP32 = 2 * (128 + 24)
 CANON_BYTES_FP64 = 2 * (256 + 24)
 
 
-# This build's own count of the flops its step kernel performs per
-# node-update, in interpolate-then-transform form:
+# A count of the flops per node-update in interpolate-then-transform form with a
+# coefficient vector per velocity (the step kernel reduces each stencil row to N + 1
+# numbers per distribution first and performs fewer):
 #   per predictor-corrector iteration: departure points and weights 112,
 #   interpolation 16 velocities x NP^2 taps x (1 weight product + 20 moments x
 #   FMA) = 10496 for the cubic stencil (NP = 4), 5904 for the quadratic one,

@@ -4,15 +4,14 @@
 // D2Q16 and pond_kernels25.hip for D2Q25 (two translation units compiled in
 // parallel); the launchers are reached through Launch<P, L>.
 //
-// Step = two launches on one stream:
-//   1. moments pre-pass: per node, the moments of f and g up to the lattice's
-//      Grad order (Eq. genericMomentUptoO3) about the instance's reference
-//      velocity, written as grouped planes;
-//   2. step: per destination node (one lane), the predictor-corrector loop
-//      (gather -> conserved sums -> new frame -> convergence test, wave exits
-//      when every lane has converged), then re-projection onto the frame of
-//      the gathered moments and BGK relaxation in Grad-coefficient space, and
-//      the store of f*, g* and the frame into the other state buffer.
+// Step = one launch: per destination node, the predictor-corrector loop (gather ->
+// conserved sums -> new frame -> convergence test, wave exits when every lane has
+// converged), then re-projection onto the frame of the gathered moments and BGK
+// relaxation in Grad-coefficient space, the store of f*, g* and the frame into the
+// other state buffer, and of their moments up to the lattice's Grad order (Eq.
+// genericMomentUptoO3) about the instance's reference velocity, as grouped planes,
+// which the next step's gather reads.  A moments pre-pass writes those of a loaded
+// state.
 // The gather evaluates Eq. propagationInterpolated through linearity: the
 // moments of the stencil nodes are interpolated at the departure point and the
 // frame transformation is applied once to the interpolated moments, instead of

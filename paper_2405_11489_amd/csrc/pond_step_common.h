@@ -142,7 +142,7 @@ __device__ __forceinline__ void store_moments(P *__restrict__ base, long long st
 // contiguously (node-major, 5 float4 = 80 B per node), so every tap and group of
 // a stencil row is reached from one address with immediate offsets; lanes
 // reading neighbouring nodes then touch disjoint banks (a stride of 20 banks).
-// The per-velocity gather (FP64, D2Q25) stages the region as grouped planes
+// FP64 and D2Q25 stage the region as grouped planes
 // instead: group k of staged node idx at vector k * cap + idx, so the lanes of
 // a wave, which read neighbouring nodes, read neighbouring vectors.  Node-major
 // tiles of those variants either share banks between lanes (D2Q25 FP32, 128 B

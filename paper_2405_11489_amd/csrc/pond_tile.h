@@ -6,19 +6,6 @@
 
 #include "pond_step_common.h"
 
-#ifndef POND_WAVES_F32
-#define POND_WAVES_F32 2
-#endif
-#ifndef POND_WAVES_F32_25
-#define POND_WAVES_F32_25 2
-#endif
-#ifndef POND_WAVES_F64
-#define POND_WAVES_F64 1
-#endif
-#ifndef POND_WAVES_F64_25
-#define POND_WAVES_F64_25 1
-#endif
-
 namespace pond {
 
 // Tap source of a tile: the moments of the block's source region (unwrapped
@@ -121,14 +108,13 @@ __device__ __forceinline__ void block_bounds(int (&v)[4], int *red) {
 }
 
 // Minimum waves per SIMD asked of the register allocator for the step kernels of
-// NT lanes per block.  FP32 D2Q16 needs 228 VGPRs: two waves (three, at 168 VGPRs,
+// NT lanes per block.  FP32 needs nearly 256 VGPRs: two waves (three, at 168 VGPRs,
 // spill 36 of them: 2048^2 quadrants 0.82 against 0.71 ms per step, 512^2 Mach 2
 // 0.117 against 0.113).  FP64 holds the weight table and a row in twice the
 // registers: one wave of 512 (two spill 130: 512^2 Mach 2 0.51 against 0.34 ms).
 template <typename P, int S, int NT = 256, class L = D2Q16>
 constexpr int step_min_waves() {
-    if (sizeof(P) == 4) return L::Q == 16 ? POND_WAVES_F32 : POND_WAVES_F32_25;
-    return L::Q == 16 ? POND_WAVES_F64 : POND_WAVES_F64_25;
+    return sizeof(P) == 4 ? 2 : 1;
 }
 
 // Blocks are dispatched round-robin over the 8 XCDs (block b on XCD b % 8);
