@@ -440,6 +440,125 @@ __device__ __forceinline__ void moments_from_lattice_sums(const P C[L::NM], P s,
     }
 }
 
+// The second moment along x (the same along y) of the float weights that an
+// equilibrium of density 1 is stored with, sum_i herm[i][0] c_ix^2: the weights sum
+// to 1 exactly, but this to 1 + 7.3e-8 on D2Q16 and 1 - 5.4e-8 on D2Q25.
+template <class L>
+constexpr double stored_second_moment() {
+    const LatticeTablesP<float, L> t = make_lattice_tables_p<float, L>();
+    double sum = 0.0;
+    for (int i = 0; i < L::Q; ++i) sum += double(t.herm[i][0]) * L::c(i / L::Q1) * L::c(i / L::Q1);
+    return sum;
+}
+static_assert(stored_second_moment<D2Q16>() - 1.0 < 1e-7 && 1.0 - stored_second_moment<D2Q16>() < 1e-7 &&
+                  stored_second_moment<D2Q25>() - 1.0 < 1e-7 &&
+                  1.0 - stored_second_moment<D2Q25>() < 1e-7,
+              "the stored weights' second moment is the lattice's to rounding");
+
+// The moments about u_ref of a node's stored populations, which the next step
+// gathers, built from its x-components in turn (add) in the frame the populations
+// are stored in (moments).  The zeroth moments are summed in FP64.
+//
+// In FP32 so are f's sums of odd order along x and its second moments along the
+// axes, these in units of stored_second_moment: a uniform flow repeats the rounding
+// of a float sum in every step, and the momentum and, in the non-translational
+// split, the temperature are read from them.  (A symmetric f had odd float sums of
+// 1e-8, which pushed the rounding of its populations one way; along y they cancel
+// pair by pair.  On D2Q25 at T = 1 the float second moments summed to 1 - 6e-8, and
+// T fell by 1.9e-5 in 2000 steps.)  100 random uniform flows of each split and
+// lattice over 2000 steps, rms errors with float sums and populations rounded term
+// by term, and with these: u / max(|u|, sqrt T) 1.5e-6 .. 2.0e-5 and 2e-14, T
+// 1.2e-7 .. 1.1e-6 and 5e-8 .. 7e-8.  They cost 1 % of the time of a step.
+template <typename P, class L>
+struct StoredMoments {
+    static constexpr int NM = L::NM, Q1 = L::Q1;
+    P Cf[NM], Cg[NM];  // lattice sums
+    double mass = 0.0, gzero = 0.0;
+    // FP32: lattice sums of f (fodd: those of odd order in x but the first)
+    double fx = 0.0, fy = 0.0, fxx = 0.0, fyy = 0.0, fodd[NM];
+    __host__ __device__ static constexpr bool odd_sum(int k) {
+        return mom_px(k) % 2 == 1 && mom_px(k) + mom_py(k) > 1;
+    }
+
+    __device__ __forceinline__ StoredMoments() {
+#pragma unroll
+        for (int k = 0; k < NM; ++k) {
+            Cf[k] = Cg[k] = P(0);
+            fodd[k] = 0.0;
+        }
+    }
+
+    __device__ __forceinline__ void add(int ia, const P (&f)[Q1], const P (&g)[Q1]) {
+        P S[L::N + 1];
+        column_sums<L>(f, S);
+        if constexpr (sizeof(P) == 4) {
+            double m = 0.0;
+#pragma unroll
+            for (int b = 0; b < Q1 / 2; ++b) {
+                const double cb = L::c(Q1 - 1 - b);
+                const double lo = double(f[b]), hi = double(f[Q1 - 1 - b]);
+                m += hi + lo;
+                fy += cb * (hi - lo);
+                fyy += (cb * cb) * (hi + lo);
+            }
+            if constexpr (Q1 % 2 == 1) m += double(f[Q1 / 2]);
+            const double ca = L::c(ia);
+            mass += m;
+            fx += ca * m;
+            fxx += (ca * ca) * m;
+            double cp = ca;
+#pragma unroll
+            for (int p = 1; p <= L::N; p += 2) {
+#pragma unroll
+                for (int q = p == 1 ? 1 : 0; p + q <= L::N; ++q)
+                    fodd[mom_index(p, q)] += cp * (q == 0 ? m : double(S[q]));
+                cp *= ca * ca;
+            }
+#pragma unroll
+            for (int b = 0; b < Q1; ++b) gzero += double(g[b]);
+        } else {
+#pragma unroll
+            for (int b = 0; b < Q1; ++b) {
+                mass += double(f[b]);
+                gzero += double(g[b]);
+            }
+        }
+        column_flush<L>(Cf, S, ia);
+        column_add<L>(Cg, g, ia);
+    }
+
+    // M[0 .. 2 NM): f's and g's moments; frame (ux, uy, T), s = sqrt T, offset
+    // (dx, dy) of its velocity from u_ref
+    __device__ __forceinline__ void moments(double s, double T, double dx, double dy, P *M) {
+        constexpr int k10 = mom_index(1, 0), k01 = mom_index(0, 1);
+        constexpr int k20 = mom_index(2, 0), k02 = mom_index(0, 2);
+        constexpr bool kSums = sizeof(P) == 4;
+        if constexpr (kSums) {
+            constexpr double unit = 1.0 / stored_second_moment<L>();
+            fxx *= unit;
+            fyy *= unit;
+            Cf[0] = P(mass);
+            Cf[k10] = P(fx);
+            Cf[k01] = P(fy);
+            Cf[k20] = P(fxx);
+            Cf[k02] = P(fyy);
+#pragma unroll
+            for (int k = 0; k < NM; ++k)
+                if (odd_sum(k)) Cf[k] = P(fodd[k]);
+        }
+        moments_from_lattice_sums<L>(Cf, P(s), P(dx), P(dy), M);
+        moments_from_lattice_sums<L>(Cg, P(s), P(dx), P(dy), M + NM);
+        M[0] = P(mass);
+        M[NM] = P(gzero);
+        if constexpr (kSums) {
+            M[k10] = P(s * fx + dx * mass);
+            M[k01] = P(s * fy + dy * mass);
+            M[k20] = P(T * fxx + dx * (2.0 * s * fx + dx * mass));
+            M[k02] = P(T * fyy + dy * (2.0 * s * fy + dy * mass));
+        }
+    }
+};
+
 // Unwrapped index range [lo, hi] of the stencils of every velocity of a node at
 // coordinate x with frame velocity u and sqrt(T) = s along one axis.
 template <int NP, class L = D2Q16>
@@ -919,22 +1038,20 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
         // moments of the stored values about u_ref (the next step's taps)
         const P sTP = P(sT), u0 = P(ln0), u1 = P(ln1);
         const double Tst = bad ? NAN : ln2, uxst = bad ? NAN : ln0, uyst = bad ? NAN : ln1;
-        const P sM = P(bad ? NAN : sT), dxM = P(uxst - a.uref_x), dyM = P(uyst - a.uref_y);
         P MM[nmom_padded<P, L>()];
 #pragma unroll
         for (int k = 0; k < nmom_padded<P, L>(); ++k) MM[k] = P(0);
-        P Nf[NM], Ng[NM];  // lattice sums (column_add)
-#pragma unroll
-        for (int k = 0; k < NM; ++k) Nf[k] = Ng[k] = P(0);
-        double mass = 0.0, gzero = 0.0;  // zeroth moments summed in FP64 (see above)
+        StoredMoments<P, L> sums;
         // x-component ia's post-collision populations, stored
         auto rebuild = [&](int ia, P (&fc)[L::Q1], P (&gc)[L::Q1]) {
 #pragma unroll
             for (int b = 0; b < L::Q1; ++b) {
                 const int i = L::Q1 * ia + b;
+                // the small terms first, the weight's last: one rounding at the
+                // population's own size, where adding them to it one by one rounds each
                 P fv = P(0), gv = P(0);
 #pragma unroll
-                for (int k = 0; k < NM; ++k) {
+                for (int k = NM - 1; k >= 0; --k) {
                     fv += tab.herm[i][k] * af[k];
                     gv += tab.herm[i][k] * ag[k];
                 }
@@ -952,15 +1069,6 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
                 gc[b] = gv;
             }
         };
-        auto gather_sums = [&](int ia, const P (&fc)[L::Q1], const P (&gc)[L::Q1]) {
-#pragma unroll
-            for (int b = 0; b < L::Q1; ++b) {
-                mass += double(fc[b]);
-                gzero += double(gc[b]);
-            }
-            column_add<L>(Nf, fc, ia);
-            column_add<L>(Ng, gc, ia);
-        };
         if constexpr (Quad) {
             P fc[L::Q1], gc[L::Q1];
             rebuild(quad, fc, gc);
@@ -972,7 +1080,7 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
                     fj[b] = quad_lane<J>(fc[b]);
                     gj[b] = quad_lane<J>(gc[b]);
                 }
-                gather_sums(J, fj, gj);
+                sums.add(J, fj, gj);
             };
             from(std::integral_constant<int, 0>{});
             from(std::integral_constant<int, 1>{});
@@ -983,13 +1091,10 @@ __device__ __forceinline__ void node_step(const StepArgs &a, const Taps &taps, i
             for (int ia = 0; ia < L::Q1; ++ia) {
                 P fc[L::Q1], gc[L::Q1];
                 rebuild(ia, fc, gc);
-                gather_sums(ia, fc, gc);
+                sums.add(ia, fc, gc);
             }
         }
-        moments_from_lattice_sums<L>(Nf, sM, dxM, dyM, MM);
-        moments_from_lattice_sums<L>(Ng, sM, dxM, dyM, MM + NM);
-        MM[0] = P(mass);
-        MM[NM] = P(gzero);
+        sums.moments(bad ? NAN : sT, Tst, uxst - a.uref_x, uyst - a.uref_y, MM);
         if (owner) {
             out_store<kStreamFrame>(&dst.ux[n], uxst);
             out_store<kStreamFrame>(&dst.uy[n], uyst);

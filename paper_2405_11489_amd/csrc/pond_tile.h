@@ -315,19 +315,13 @@ __device__ __forceinline__ void tile_step(const StepArgs &a, DevState src, const
 template <typename P, class L = D2Q16>
 __device__ __forceinline__ void node_moments(const StepArgs &a, DevState st, P *__restrict__ mom,
                                              long long n) {
-    double sd, isd;
-    frame_scale(st.T[n], sd, isd);
-    const P s = P(sd);
-    const P dx = P(st.ux[n] - a.uref_x), dy = P(st.uy[n] - a.uref_y);
-    constexpr int NM = L::NM;
+    const double T = st.T[n];
+    double s, is;
+    frame_scale(T, s, is);
     P M[nmom_padded<P, L>()];
 #pragma unroll
     for (int k = 0; k < nmom_padded<P, L>(); ++k) M[k] = P(0);
-    // through the lattice sums, in the order the step forms them (the same bits)
-    P Cf[NM], Cg[NM];
-#pragma unroll
-    for (int k = 0; k < NM; ++k) Cf[k] = Cg[k] = P(0);
-    double mass = 0.0, gzero = 0.0;  // zeroth moments summed in FP64, as the step does
+    StoredMoments<P, L> sums;  // as the step forms them (the same bits)
 #pragma unroll
     for (int ia = 0; ia < L::Q1; ++ia) {
         P fc[L::Q1], gc[L::Q1];
@@ -336,16 +330,10 @@ __device__ __forceinline__ void node_moments(const StepArgs &a, DevState st, P *
             const int i = L::Q1 * ia + b;
             fc[b] = pop_plane<P>(st.f, i, a.N)[n];
             gc[b] = pop_plane<P>(st.g, i, a.N)[n];
-            mass += double(fc[b]);
-            gzero += double(gc[b]);
         }
-        column_add<L>(Cf, fc, ia);
-        column_add<L>(Cg, gc, ia);
+        sums.add(ia, fc, gc);
     }
-    moments_from_lattice_sums<L>(Cf, s, dx, dy, M);
-    moments_from_lattice_sums<L>(Cg, s, dx, dy, M + NM);
-    M[0] = P(mass);
-    M[NM] = P(gzero);
+    sums.moments(s, T, st.ux[n] - a.uref_x, st.uy[n] - a.uref_y, M);
     store_moments<P, nmom<L>()>(mom, a.mstride, a.moff + n, M);
 }
 
