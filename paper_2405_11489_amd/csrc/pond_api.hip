@@ -139,13 +139,15 @@ static long long tiles_of(const pond_params &p, int tx, int ty) {
 
 // Block shape: 64 x 1 rows for (quasi-)one-dimensional grids, else 32 x 8.
 // D2Q16 takes the 512-lane 32 x 16 tile in FP64 when its tiles cover every CU (one
-// block per CU holds the whole LDS; 512^2, Mach 2: 0.29 ms per step against 0.34
-// with 32 x 8; at 256^2 its 128 tiles leave half the CUs idle: 0.132 against 0.085),
-// and in FP32 when the grid needs more than one round of 32 x 8 blocks but fits one
-// round of 32 x 16 blocks (a kernel that runs more waves per SIMD with 512-lane
-// blocks than with 256-lane ones; two either way as built, so it keeps 32 x 8:
-// 2048^2 quadrants 0.81 against 0.85 ms, 512^2 Mach 2 0.113 against 0.114).
-pond_tuning default_tuning(const pond_params &p, int reach) {
+// block per CU holds the whole LDS; 512^2, Mach 2: 0.30 ms per step against 0.31
+// with 32 x 8; at 256^2 its 128 tiles leave half the CUs idle: 0.143 against 0.085)
+// and the source region of a flow of this temperature fits the LDS, else 16 x 16,
+// which carries less halo (T = 1.4, Mach 2: 0.30 against 0.43 ms; T = 4: 0.52
+// against 0.74); and in FP32 when the grid needs more than one round of 32 x 8 blocks
+// but fits one round of 32 x 16 blocks (a kernel that runs more waves per SIMD with
+// 512-lane blocks than with 256-lane ones; two either way as built, so it keeps
+// 32 x 8: 2048^2 quadrants 0.75 against 0.80 ms, 512^2 Mach 2 0.107 against 0.114).
+pond_tuning default_tuning(const pond_params &p, int reach, double thermal_reach) {
     pond_tuning t;
     t.kernel = POND_KERNEL_TILED;
     const bool dbl = p.precision == POND_PREC_FP64;
@@ -156,7 +158,10 @@ pond_tuning default_tuning(const pond_params &p, int reach) {
         if (p.lattice == POND_LATTICE_D2Q16 && p.ny >= 16) {
             const long long cus = device_cus();
             if (dbl) {
-                if (cus > 0 && tiles_of(p, 32, 16) >= cus) t.tile = POND_TILE_32x16;
+                const double halo = 2.0 * thermal_reach + p.interp_points;
+                const bool fits = (32.0 + halo) * (16.0 + halo) <= lds_nodes_for_blocks(1, true);
+                if (cus > 0 && tiles_of(p, 32, 16) >= cus)
+                    t.tile = fits ? POND_TILE_32x16 : POND_TILE_16x16;
             } else {
                 const long long cap8 =
                     cus * tiled_blocks_per_cu(p.lattice, false, p.interp_points, p.split,
@@ -374,15 +379,16 @@ pond_status check_unbatched(const pond_ctx *c) {
     return POND_OK;
 }
 
-// Stencil reach of the frame just loaded (from cnt->partial[3]) and, unless the
+// Stencil reach of the frame just loaded (from cnt->partial[3 .. 4]) and, unless the
 // tuning was set explicitly, the autotuned configuration of the context's class or
 // the default for that reach.
 pond_status finish_init(pond_ctx *c, const DevCounters &h) {
     const double r = std::ceil(h.partial[3]);
     c->reach = r > 1e6 ? 1000000 : int(r);
+    c->thermal_reach = h.partial[4];
     if (c->user_tuned) return POND_OK;
     pond_tuning t;
-    if (!tuning_cache_lookup(c, &t)) t = default_tuning(c->p, c->reach);
+    if (!tuning_cache_lookup(c, &t)) t = default_tuning(c->p, c->reach, c->thermal_reach);
     return apply_tuning(c, t);
 }
 

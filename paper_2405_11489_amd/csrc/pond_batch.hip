@@ -706,7 +706,8 @@ pond_status pond_autotune(pond_ctx *c, int steps, pond_tuning *out) {
         tiles = {POND_TILE_64x1, POND_TILE_256x1};
         widths = {256};
     } else {
-        tiles = {default_tuning(c->p, c->reach).tile, POND_TILE_32x8, POND_TILE_16x16, POND_TILE_16x8};
+        tiles = {default_tuning(c->p, c->reach, c->thermal_reach).tile, POND_TILE_32x8,
+                 POND_TILE_16x16, POND_TILE_16x8};
         if (c->p.lattice == POND_LATTICE_D2Q16) tiles.push_back(POND_TILE_32x16);
         // one-wave blocks: each wave frees its CU share as soon as it is done, which
         // pays where the predictor-corrector work varies from wave to wave (shocks:

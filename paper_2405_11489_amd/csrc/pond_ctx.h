@@ -38,7 +38,7 @@ struct Layout {
 // along trajectories from the last two levels; 0 otherwise.
 inline int prev_frame_planes(int split) { return split == POND_SPLIT_INTERNAL ? 2 : 0; }
 
-constexpr int kScratchDoubles = 4 * 256;
+constexpr int kScratchDoubles = 5 * 256;
 
 // Values of a node's moment groups (2 NM moments, padded): 20 on D2Q16; on
 // D2Q25 32 floats or 30 doubles.
@@ -67,9 +67,9 @@ int lds_nodes_for_blocks(int blocks_per_cu, bool dbl, int lattice = 16);
 // LDS nodes per block of the tiled kernel's default share for a tile shape.
 int default_lds_nodes(int tile, const pond_params &p);
 // Default launch configuration of a context with these parameters (on the
-// current device); reach: the stencil reach of its initial frame in nodes, 0 if
-// it is not known.
-pond_tuning default_tuning(const pond_params &p, int reach = 0);
+// current device); reach: the stencil reach of its initial frame in nodes, and
+// thermal_reach its thermal part c_out sqrt(T), 0 if they are not known.
+pond_tuning default_tuning(const pond_params &p, int reach = 0, double thermal_reach = 0.0);
 
 // POND_OK, or the status and message (pond_last_error) of the first invalid or
 // unsupported parameter.  Touches no device.
@@ -117,6 +117,7 @@ struct pond_ctx {
     long long prof_launches;
     pond_batch *batch;  // batch that owns the stepping of this context, or NULL
     int reach;          // ceil of the largest stencil reach of the initial frame (nodes)
+    double thermal_reach;  // its largest c_out sqrt(T)
     bool user_tuned;    // tuning set explicitly: the tuning cache does not override it
 };
 

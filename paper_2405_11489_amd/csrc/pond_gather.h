@@ -208,15 +208,16 @@ struct RowReader {
             for (int k = k0; k < k1; ++k) buf[c % 2][p - p0][k - k0] = row(k, p);
     }
 
-    // x-interpolation of the loaded chunk c into X
-    __device__ __forceinline__ void interpolate(int c, const P wx[NP],
+    // x-interpolation of the row's loaded chunk c into X
+    template <class Row>
+    __device__ __forceinline__ void interpolate(const Row &row, int c, const P wx[NP],
                                                 P X[MV::G * MV::W]) const {
         const int k0 = c < CH ? 0 : GF, k1 = c < CH ? GF : MV::G, p0 = (c % CH) * CT;
 #pragma unroll
         for (int p = p0; p < p0 + CT && p < NP; ++p)
 #pragma unroll
             for (int k = k0; k < k1; ++k) {
-                const V v = buf[c % 2][p - p0][k - k0];
+                const V v = row.deviation(k, buf[c % 2][p - p0][k - k0]);
                 const P w = wx[p];
                 P *x = X + MV::W * k;
                 x[0] = p == 0 ? w * v.x : x[0] + w * v.x;
@@ -229,23 +230,21 @@ struct RowReader {
     }
 
     // One row, whose first chunk is loaded: f's moments are interpolated along x
-    // and reduced, then g's, w[b] times the result added to af and ag.  advance()
-    // moves row to the row whose first chunk is to be read ahead.
-    template <class Row, class Advance>
-    __device__ __forceinline__ void row(Row &row, Advance &&advance, const P wx[NP],
+    // and reduced, then g's, w[b] times the result added to af and ag.  ahead()
+    // loads the first chunk of the row to visit next, if it is to be read ahead.
+    template <class Row, class Ahead>
+    __device__ __forceinline__ void row(const Row &row, Ahead &&ahead, const P wx[NP],
                                         const P al[L::NM], const YFactors<P, L> &y,
                                         const P w[L::Q1], P af[L::Q1], P ag[L::Q1]) {
         P X[MV::G * MV::W], D[L::N + 1];
 #pragma unroll
         for (int c = 0; c < 2 * CH; ++c) {
-            if (c + 1 < 2 * CH) {
+            if (c + 1 < 2 * CH)
                 load(row, c + 1);
-            } else {
-                advance();
-                load(row, 0);
-            }
+            else
+                ahead();
             __builtin_amdgcn_sched_barrier(0);
-            interpolate(c, wx, X);
+            interpolate(row, c, wx, X);
             if (c == CH - 1 || c == 2 * CH - 1) {
                 row_factors<P, L>(X + (c < CH ? 0 : L::NM), al, y, D);
                 add_row<P, L>(D, w, c < CH ? af : ag);
@@ -255,32 +254,6 @@ struct RowReader {
     }
 };
 
-// One row of the general gather, column by column in few registers: load(p, M)
-// reads the moments in column p.
-template <typename P, int NP, class L, class Load>
-__device__ __forceinline__ void general_row(const Load &load, const P wx[NP], const P al[L::NM],
-                                            const YFactors<P, L> &y, const P w[L::Q1],
-                                            P af[L::Q1], P ag[L::Q1]) {
-    using MV = MomVec<P, nmom<L>()>;
-    P X[MV::G * MV::W], D[L::N + 1];
-#pragma unroll
-    for (int k = 0; k < MV::G * MV::W; ++k) X[k] = P(0);
-#pragma unroll 1
-    for (int p = 0; p < NP; ++p) {
-        P wp = wx[0];
-#pragma unroll
-        for (int j = 1; j < NP; ++j) wp = p == j ? wx[j] : wp;
-        P M[MV::G * MV::W];
-        load(p, M);
-#pragma unroll
-        for (int k = 0; k < 2 * L::NM; ++k) X[k] += wp * M[k];
-    }
-    row_factors<P, L>(X, al, y, D);
-    add_row<P, L>(D, w, af);
-    row_factors<P, L>(X + L::NM, al, y, D);
-    add_row<P, L>(D, w, ag);
-}
-
 // Columns per chunk.  Two chunks of two columns (FP32 D2Q16: six loads of 16 bytes
 // in flight) cover the LDS latency: whole rows took 80 more registers and the same
 // time (512^2 Mach 2: 0.1108 against 0.1106 ms per step).
@@ -288,8 +261,9 @@ template <int NP>
 constexpr int chunk_columns() { return NP < 2 ? NP : 2; }
 
 // Rows of the unrolled gather: the union of an x-component's row stencils when
-// its velocities' first rows lie within NP + 2 rows of each other (D2Q16: 2 c_out
-// sqrt T < 6 by position, T up to 1.2 for certain).
+// its velocities' first rows lie within NP + 2 rows of each other: for certain where
+// 2 c_out sqrt T <= NP + 2 (D2Q16: T <= 1.65 with the cubic stencil, 1.14 with the
+// quadratic one; D2Q25: T <= 1.10), by position below NP + 3 (T < 2.25, 1.65; 1.50).
 template <int NP>
 constexpr int table_rows() { return 2 * NP + 2; }
 
@@ -314,8 +288,13 @@ __device__ __forceinline__ void unrolled_rows(RowReader<P, NP, L, CT> &rd, Row &
                                               bool flat, const P wx[NP], const P al[L::NM],
                                               const YFactors<P, L> &y, const P (&wt)[RS][L::Q1],
                                               P af[L::Q1], P ag[L::Q1]) {
-    rd.row(at, [&] { if (R + 1 < NP ? !flat : span > R + 1) at.next(); }, wx, al, y, wt[R], af,
-           ag);
+    rd.row(
+        at,
+        [&] {
+            if (R + 1 < NP ? !flat : span > R + 1) at.next();
+            rd.load(at, 0);
+        },
+        wx, al, y, wt[R], af, ag);
     if constexpr (R + 1 < RS) {
         if (R == 0 && flat) return;
         if (R + 1 >= NP && __ballot(span > R + 1) == 0) return;
@@ -323,8 +302,14 @@ __device__ __forceinline__ void unrolled_rows(RowReader<P, NP, L, CT> &rd, Row &
     }
 }
 
-// The gather of x-component ia by per-velocity queues of row weights, from
-// wherever the rows are (see gather_rows).
+// The gather of x-component ia by per-velocity queues of row weights, one row at a
+// time: staged rows with read-ahead where the x-component's rows are all staged in
+// every lane of the wave, else rows in HBM.  One column per chunk: two take registers
+// that the unrolled rows need (D2Q25 FP64 spilled, 0.43 against 0.35 ms per step of
+// 384^2 at T = 1).  Reading rows that are half staged from either place took longer
+// than from HBM alone (D2Q25 at T = 3, Mach 2: FP32 0.58 against 0.50 ms, FP64 1.84
+// against 1.45), and so did rows column by column without read-ahead (D2Q16 512^2 at
+// T = 2, FP32: 0.226 against 0.144 ms; FP64 0.91 against 0.43).
 template <typename P, int NP, class L, class Taps>
 __device__ __forceinline__ void gather_general(const Taps &taps, int ia, double xu, double yu,
                                                double sc, const XFrame<P, L> &xf,
@@ -348,19 +333,44 @@ __device__ __forceinline__ void gather_general(const Taps &taps, int ia, double 
     // the union's rows in turn, every velocity whose stencil holds the row; a union
     // longer than the separate stencils velocity by velocity
     const bool whole = span <= Q1 * NP;
+    auto take = [&](int b, bool on, P (&w)[Q1]) {  // velocity b's weight of this row
+        w[b] = on ? q[b][0] : P(0);
+#pragma unroll
+        for (int k = 0; k + 1 < NP; ++k) q[b][k] = on ? q[b][k + 1] : q[b][k];
+        q[b][NP - 1] = on ? P(0) : q[b][NP - 1];
+    };
+    if (Taps::kStaged && __ballot(!(whole && taps.inside(bx, NP, flat ? 0 : by[Q1 - 1], span))) == 0) {
+        RowReader<P, NP, L, 1> rd;
+        auto at = taps.staged(bx, flat ? 0 : by[Q1 - 1]);
+        rd.load(at, 0);
+#pragma unroll 1
+        for (int t = 0; __ballot(t < span) != 0; ++t) {
+            P w[Q1];
+#pragma unroll
+            for (int b = 0; b < Q1; ++b) take(b, flat || t >= by[b] - by[Q1 - 1], w);
+            rd.row(
+                at,
+                [&] {  // a lane's last row again after its last
+                    if (t + 1 < span) at.next();
+                    rd.load(at, 0);
+                },
+                wx, al, y, w, af, ag);
+        }
+        return;
+    }
     int v = Q1 - 1, r = flat ? 0 : by[Q1 - 1], left = whole ? span : NP;
 #pragma unroll 1
     for (;;) {
+        RowReader<P, NP, L, 1> rd;
         P w[Q1];
+        auto weights = [&] {
 #pragma unroll
-        for (int b = 0; b < Q1; ++b) {
-            const bool on = whole ? flat || r >= by[b] : v == b;
-            w[b] = on ? q[b][0] : P(0);
-#pragma unroll
-            for (int k = 0; k + 1 < NP; ++k) q[b][k] = on ? q[b][k + 1] : q[b][k];
-            q[b][NP - 1] = on ? P(0) : q[b][NP - 1];
-        }
-        general_row<P, NP, L>([&](int p, P *M) { taps.read(bx + p, r, M); }, wx, al, y, w, af, ag);
+            for (int b = 0; b < Q1; ++b) take(b, whole ? flat || r >= by[b] : v == b, w);
+        };
+        weights();
+        const auto at = taps.outside(bx, r);
+        rd.load(at, 0);
+        rd.row(at, [] {}, wx, al, y, w, af, ag);
         ++r;
         if (--left == 0) {
             if (whole || v == 0) break;
@@ -390,11 +400,13 @@ __device__ __forceinline__ void gather_general(const Taps &taps, int ia, double 
 // stencils, each visited once.  Where that union has at most table_rows and the
 // node's stencils lie in the staged region, the row loop is unrolled over a
 // table of row weights (zero where a velocity's stencil does not hold the row)
-// that serves all x-components; otherwise the weights are shifted out of
-// per-velocity queues row by row.  A union longer than the separate stencils
-// (very hot flows) is visited stencil by stencil.  The sums are the same numbers either way: each velocity's rows
-// are added in ascending order, the others add zero.  On a single-row grid
-// every stencil row is that row, and the weights sum to one.
+// that serves all x-components; a wave with a node where that is not so shifts the
+// weights out of per-velocity queues row by row (gather_general), for all its
+// nodes: both paths one after the other would take the sum of their times.  A union
+// longer than the separate stencils (very hot flows) is visited stencil by stencil.
+// The sums are the same numbers either way: each velocity's rows are added in
+// ascending order, the others add zero.  On a single-row grid every stencil row is
+// that row, and the weights sum to one.
 //
 // Quad: this lane gathers x-component threadIdx.x % 4 alone.
 template <typename P, int NP, class L, bool Quad, class Taps, class Column>
@@ -414,7 +426,18 @@ __device__ __forceinline__ void gather_rows(const Taps &taps, double xu, double 
     const int r0 = flat ? 0 : by[Q1 - 1], span = flat ? 1 : by[0] - by[Q1 - 1] + NP;
     const int x0 = stencil_base<NP>(fma(-sc, L::c(Q1 - 1), xu));
     const int x1 = stencil_base<NP>(fma(-sc, L::c(0), xu));
-    if (span <= RS && taps.inside(x0, x1 + NP - x0, r0, span)) {
+    const bool fits = span <= RS && taps.inside(x0, x1 + NP - x0, r0, span);
+    // How likely the unrolled rows are, for the register allocator: it takes the loops
+    // of the other path for the hot ones and spills here for them unless told (2048^2
+    // quadrants 0.77 ms per step, 0.73 when told; hot flows of T = 4 0.164 and 0.174 of
+    // 512^2).  In FP64 the surer it is the more it spills there (D2Q16 512^2 0.30 when
+    // sure, 0.28 so, T = 4 0.52 and 0.48), and on D2Q25 in any case (400^2 0.43 untold,
+    // 0.48 so).
+    const bool unroll = __ballot(!fits) == 0;
+    if (Taps::kStaged &&
+        (sizeof(P) == 4 ? __builtin_expect(unroll, 1)
+                        : L::Q == 25 ? unroll
+                                     : __builtin_expect_with_probability(unroll, 1, 0.99))) {
         P wt[RS][Q1];
 #pragma unroll
         for (int b = 0; b < Q1; ++b) {

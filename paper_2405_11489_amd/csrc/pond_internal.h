@@ -36,7 +36,7 @@ struct DevCounters {
     // node-steps (or, at initialisation, nodes) whose departure stencil reached
     // beyond the ghost rows of a wall
     unsigned long long ghost_overrun;
-    double partial[4];  // scratch for deterministic reductions
+    double partial[5];  // scratch for deterministic reductions
     struct alignas(64) Slot {
         unsigned long long pc_iterations, nonconverged, nonphysical, ghost_overrun;
     } slot[kCounterSlots];
@@ -183,8 +183,8 @@ template <typename P>
 hipError_t launch_import(const StepArgs &a, const double *f, const double *g, const double *frame,
                          DevState st, hipStream_t s);
 // Of fields: the sums of rho, rho ux, rho uy (fixed summation order) into
-// cnt->partial[0..2] and the largest stencil reach max(|u_x|, |u_y|) + c_out sqrt(T)
-// into cnt->partial[3].
+// cnt->partial[0..2], the largest stencil reach max(|u_x|, |u_y|) + c_out sqrt(T)
+// into cnt->partial[3] and the largest c_out sqrt(T) into cnt->partial[4].
 hipError_t launch_field_sums(long long N, const double *rho, const double *ux, const double *uy,
                              const double *T, double *scratch, int scratch_len, DevCounters *cnt,
                              hipStream_t s);

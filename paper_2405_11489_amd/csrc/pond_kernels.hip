@@ -28,41 +28,44 @@ using lk::partial_sums_kernel;
 // ------------------------------------------- deterministic reductions ----
 constexpr int kRedBlocks = 256;
 
-// reach of a node's departure stencils, in nodes; 0 if not finite
-__device__ __forceinline__ double node_reach(double ux, double uy, double T) {
-    const double r = fmax(fabs(ux), fabs(uy)) + c1(3) * sqrt(fmax(T, 0.0));
-    return isfinite(r) ? r : 0.0;
-}
-
-// per-block maxima of max(|u_x|, |u_y|) + c_out sqrt(T); non-finite values are skipped
+// per-block maxima of the reach of a node's departure stencils in nodes, max(|u_x|,
+// |u_y|) + c_out sqrt(T), and of its thermal part; non-finite values are skipped
 __global__ __launch_bounds__(kBlock) void reach_partial_kernel(long long N, const double *ux,
                                                                const double *uy, const double *T,
                                                                double *scratch) {
-    __shared__ double sh[kBlock];
+    __shared__ double sh[2][kBlock];
     const long long chunk = (N + gridDim.x - 1) / gridDim.x;
     const long long lo = (long long)blockIdx.x * chunk;
     const long long hi = lo + chunk < N ? lo + chunk : N;
-    double m = 0.0;
-    for (long long n = lo + threadIdx.x; n < hi; n += blockDim.x)
-        m = fmax(m, node_reach(ux[n], uy[n], T[n]));
-    sh[threadIdx.x] = m;
+    double m = 0.0, mt = 0.0;
+    for (long long n = lo + threadIdx.x; n < hi; n += blockDim.x) {
+        const double rt = c1(3) * sqrt(fmax(T[n], 0.0)), r = fmax(fabs(ux[n]), fabs(uy[n])) + rt;
+        if (isfinite(r)) {
+            m = fmax(m, r);
+            mt = fmax(mt, rt);
+        }
+    }
+    const int t = threadIdx.x;
+    sh[0][t] = m;
+    sh[1][t] = mt;
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + w]);
+        if (t < w)
+            for (int c = 0; c < 2; ++c) sh[c][t] = fmax(sh[c][t], sh[c][t + w]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) scratch[blockIdx.x] = sh[0];
+    if (t < 2) scratch[t * gridDim.x + blockIdx.x] = sh[t][0];
 }
 
 // The blocks' partial results to cnt->partial: the sums of (rho, rho u) if `sums`
-// is given, in block order, and the largest reach.  One block stages the partial
+// is given, in block order, and the largest reaches.  One block stages the partial
 // results in LDS, where the in-order sums cost an add each instead of a memory
 // round trip (one thread over global memory: 28 us for the sums, 16 us for the
 // reach; this: 4.7 us for both, most of it the launch).
 __global__ __launch_bounds__(kRedBlocks) void reduce_final_kernel(const double *sums,
                                                                   const double *reach,
                                                                   DevCounters *cnt) {
-    __shared__ double sh[4][kRedBlocks + 1];
+    __shared__ double sh[5][kRedBlocks + 1];
     const int t = threadIdx.x;
     if (sums)
         for (int c = 0; c < 3; ++c) {
@@ -70,6 +73,7 @@ __global__ __launch_bounds__(kRedBlocks) void reduce_final_kernel(const double *
             sh[i % 3][i / 3] = sums[i];
         }
     sh[3][t] = reach[t];
+    sh[4][t] = reach[kRedBlocks + t];
     __syncthreads();
     if (sums && t < 3) {
         double s = 0.0;
@@ -77,11 +81,12 @@ __global__ __launch_bounds__(kRedBlocks) void reduce_final_kernel(const double *
         for (int b = 0; b < kRedBlocks; ++b) s += sh[t][b];
         cnt->partial[t] = s;
     }
-    if (t == 64) {
+    if (t == 64 || t == 65) {
+        const int c = t - 64 + 3;
         double m = 0.0;
 #pragma unroll 16
-        for (int b = 0; b < kRedBlocks; ++b) m = fmax(m, sh[3][b]);
-        cnt->partial[3] = m;
+        for (int b = 0; b < kRedBlocks; ++b) m = fmax(m, sh[c][b]);
+        cnt->partial[c] = m;
     }
 }
 
@@ -185,7 +190,7 @@ hipError_t launch_import(const StepArgs &a, const double *f, const double *g, co
 hipError_t launch_field_sums(long long N, const double *rho, const double *ux, const double *uy,
                              const double *T, double *scratch, int scratch_len, DevCounters *cnt,
                              hipStream_t s) {
-    if (scratch_len < 4 * kRedBlocks) return hipErrorInvalidValue;
+    if (scratch_len < 5 * kRedBlocks) return hipErrorInvalidValue;
     double *reach = scratch + 3 * kRedBlocks;
     hipLaunchKernelGGL(partial_sums_kernel<FieldLoader>, dim3(kRedBlocks), dim3(kBlock), 0, s, N,
                        FieldLoader{rho, ux, uy}, scratch);
@@ -198,7 +203,7 @@ hipError_t launch_field_sums(long long N, const double *rho, const double *ux, c
 template <typename P>
 hipError_t launch_state_sums(const StepArgs &a, DevState st, bool mean, double *scratch,
                              int scratch_len, DevCounters *cnt, hipStream_t s) {
-    if (scratch_len < 4 * kRedBlocks) return hipErrorInvalidValue;
+    if (scratch_len < 5 * kRedBlocks) return hipErrorInvalidValue;
     double *reach = scratch + 3 * kRedBlocks;
     if (mean) {
         hipError_t e = a.lattice == 25

@@ -168,30 +168,6 @@ constexpr unsigned lds_node_bytes() {
 }
 
 template <typename P, class L>
-__device__ __forceinline__ void load_node_lds(const P *lds, int idx, int cap, P *M) {
-    if constexpr (lds_planar<P, L>()) {
-        load_moments<P, nmom<L>()>(lds, cap, idx, M);
-        return;
-    }
-    using MV = MomVec<P, nmom<L>()>;
-    using V = typename MV::V;
-    const V *b = reinterpret_cast<const V *>(lds) + idx * lds_stride<P, L>();
-#pragma unroll
-    for (int k = 0; k < MV::G; ++k) {
-        const V v = b[k];
-        if constexpr (MV::W == 4) {
-            M[4 * k] = v.x;
-            M[4 * k + 1] = v.y;
-            M[4 * k + 2] = v.z;
-            M[4 * k + 3] = v.w;
-        } else {
-            M[2 * k] = v.x;
-            M[2 * k + 1] = v.y;
-        }
-    }
-}
-
-template <typename P, class L>
 __device__ __forceinline__ void store_node_lds(P *lds, int idx, int cap, const P *M) {
     if constexpr (lds_planar<P, L>()) {
         store_moments<P, nmom<L>()>(lds, cap, idx, M);
@@ -282,6 +258,7 @@ template <typename P, int NP, class L = D2Q16>
 struct GlobalTaps {
     using MV = MomVec<P, nmom<L>()>;
     using V = typename MV::V;
+    static constexpr bool kStaged = false;  // no rows in LDS
     const P *mom;
     long long N;  // nodes per moment plane
     int nx, ny, bc_x, bc_y;
@@ -299,22 +276,39 @@ struct GlobalTaps {
     __device__ __forceinline__ bool flat() const { return ny == 1 && bc_y != 2; }
     __device__ __forceinline__ bool inside(int, int, int, int) const { return false; }
 
-    // the moments of the (unwrapped) grid node (x, y), as deviations from the
-    // reference node's
-    __device__ __forceinline__ void read(int x, int y, P *M) const {
-        const long long row = moff + (long long)mom_row(y, ny, bc_y, wall_h) * nx;
-        load_moments<P, nmom<L>()>(mom, N, row + wrap_index(x, nx, bc_x), M);
-        if constexpr (deviations<P>()) {
-#pragma unroll
-            for (int k = 0; k < nmom<L>(); ++k) M[k] -= ref[k];
-        }
-    }
-    // nothing is staged (never called: inside() is false)
+    // A row in HBM, columns bx .. bx + NP - 1 of the (unwrapped) grid row y: (k, p) is
+    // moment group k in column p, deviation(k, v) the group's value v as deviations
+    // from the reference node's.
     struct Row {
-        __device__ __forceinline__ V operator()(int, int) const { return V{}; }
-        __device__ __forceinline__ void next() {}
+        const V *base;
+        long long N;
+        int col[NP];
+        const P *ref;
+        __device__ __forceinline__ V operator()(int k, int p) const {
+            return base[k * N + col[p]];
+        }
+        __device__ __forceinline__ V deviation(int k, V v) const {
+            if constexpr (deviations<P>()) {
+                v.x -= ref[4 * k];
+                v.y -= ref[4 * k + 1];
+                v.z -= ref[4 * k + 2];
+                v.w -= ref[4 * k + 3];
+            }
+            return v;
+        }
+        __device__ __forceinline__ void next() {}  // unused: rows in HBM are visited one by one
     };
-    __device__ __forceinline__ Row staged(int, int) const { return Row{}; }
+    __device__ __forceinline__ Row outside(int bx, int y) const {
+        Row r;
+        r.base = reinterpret_cast<const V *>(mom) + moff + (long long)mom_row(y, ny, bc_y, wall_h) * nx;
+        r.N = N;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) r.col[p] = wrap_index(bx + p, nx, bc_x);
+        r.ref = ref;
+        return r;
+    }
+    // nothing is staged
+    __device__ __forceinline__ Row staged(int bx, int y) const { return outside(bx, y); }
 };
 
 // How many lanes gather a node (node_step).

@@ -17,6 +17,7 @@ template <typename P, int NP, class L = D2Q16>
 struct TileTaps {
     using MV = MomVec<P, nmom<L>()>;
     using V = typename MV::V;
+    static constexpr bool kStaged = true;
     const P *lds;
     int cap, X0, Y0, X1, Y1, W;
     GlobalTaps<P, NP, L> glob;
@@ -45,6 +46,7 @@ struct TileTaps {
                                                     unsigned(p) * lds_node_bytes<P, L>() +
                                                     unsigned(k * sizeof(V)));
         }
+        __device__ __forceinline__ V deviation(int, V v) const { return v; }  // staged as such
         __device__ __forceinline__ void next() { off += pitch; }
     };
     __device__ __forceinline__ Row staged(int bx, int r) const {
@@ -55,15 +57,7 @@ struct TileTaps {
                        unsigned(__umul24(unsigned(bx - X0), NB)),
                    pitch, cap};
     }
-    // the moments of grid node (x, y), from the staged region or HBM
-    __device__ __forceinline__ void read(int x, int y, P *M) const {
-        if (inside(x, 1, y, 1)) {
-            const int idx = __umul24(unsigned(flat() ? 0 : y - Y0), unsigned(W)) + (x - X0);
-            load_node_lds<P, L>(lds, idx, cap, M);
-        } else {
-            glob.read(x, y, M);
-        }
-    }
+    __device__ __forceinline__ auto outside(int bx, int r) const { return glob.outside(bx, r); }
 };
 
 // Ints of shared memory of block_bounds for a block of NT lanes: four per wave.
