@@ -111,15 +111,20 @@ pond_status write_counters(pond_ctx *c, const DevCounters &in) {
 // blocks that fit by registers.  A 32 x 8 tile at T = 1, Mach 2 needs a
 // 40 x 16 source region.
 int default_lds_nodes(int tile, const pond_params &p) {
+    return lds_nodes_for_blocks(tile_blocks_per_cu(p, tile), p.precision == POND_PREC_FP64,
+                                p.lattice);
+}
+
+bool runs_quad_lanes(const pond_params &p, int tile) {
+    return p.lattice == POND_LATTICE_D2Q16 && (tile == POND_TILE_8x8 || tile == POND_TILE_64x1) &&
+           quad_lanes((long long)p.nx * p.ny, p.precision == POND_PREC_FP64);
+}
+
+int tile_blocks_per_cu(const pond_params &p, int tile) {
     const bool dbl = p.precision == POND_PREC_FP64;
-    const bool quad = p.lattice == POND_LATTICE_D2Q16 &&
-                      (tile == POND_TILE_8x8 || tile == POND_TILE_64x1) &&
-                      quad_lanes((long long)p.nx * p.ny, dbl);
-    return lds_nodes_for_blocks(
-        quad ? quad_blocks_per_cu(dbl)
-             : tiled_blocks_per_cu(p.lattice, dbl, p.interp_points, p.split,
-                                   static_cast<TileShape>(tile)),
-        dbl, p.lattice);
+    return runs_quad_lanes(p, tile) ? quad_blocks_per_cu(dbl)
+                                    : tiled_blocks_per_cu(p.lattice, dbl, p.interp_points, p.split,
+                                                          static_cast<TileShape>(tile));
 }
 
 // Compute units of the current device (0 if the query fails).

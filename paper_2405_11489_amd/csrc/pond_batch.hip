@@ -159,7 +159,9 @@ const void *batch_step_fn(bool dbl, int np, int split, int lattice) {
 // ----------------------------------------------------- tuning cache ----
 // Class of an instance: lattice, energy split, precision, stencil, boundary
 // conditions, the rounded log2 of each axis (a single-row grid is its own
-// class) and the stencil reach of its initial frame (the best tile shape
+// class), whether its 64-node tiles run four lanes per node (another kernel, whose
+// tile and LDS share would leave a larger grid of the class one or two single-wave
+// blocks per CU), and the stencil reach of its initial frame (the best tile shape
 // depends on the halo).
 using TuneKey = std::tuple<int, int, int, int, int>;
 std::mutex g_tune_mu;
@@ -170,7 +172,8 @@ int log2_class(int n) { return n <= 1 ? -1 : int(std::lround(std::log2(double(n)
 TuneKey tune_key(const pond_ctx *c) {
     const pond_params &p = c->p;
     // lattices tune apart: a D2Q16 class may pick a tile D2Q25 does not run
-    return TuneKey(p.lattice * 1024 + p.split * 64 + p.precision * 16 + p.interp_points,
+    const int quad = runs_quad_lanes(p, POND_TILE_8x8) ? 8 : 0;
+    return TuneKey(p.lattice * 1024 + p.split * 64 + p.precision * 16 + quad + p.interp_points,
                    p.bc_x * 2 + p.bc_y, log2_class(p.nx), log2_class(p.ny),
                    std::min(c->reach, 12));
 }
@@ -728,8 +731,7 @@ pond_status pond_autotune(pond_ctx *c, int steps, pond_tuning *out) {
     std::vector<Cand> cands;
     for (int tile : tiles) {
         cands.push_back({tile, 0});
-        const int blocks = tiled_blocks_per_cu(c->p.lattice, dbl, c->p.interp_points, c->p.split,
-                                               static_cast<TileShape>(tile));
+        const int blocks = tile_blocks_per_cu(c->p, tile);
         if (blocks >= 2)
             cands.push_back({tile, lds_nodes_for_blocks(blocks - 1, dbl, c->p.lattice)});
     }

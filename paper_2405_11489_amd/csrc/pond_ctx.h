@@ -64,6 +64,10 @@ Layout layout_for(long long N, size_t psize, int lattice, long long mom_nodes, i
 // LDS nodes per block (the moment groups of one node each) that let
 // blocks_per_cu blocks share the 160 KiB of a CU.
 int lds_nodes_for_blocks(int blocks_per_cu, bool dbl, int lattice = 16);
+// Whether a grid runs a tile shape with four lanes per node (quad_lanes).
+bool runs_quad_lanes(const pond_params &p, int tile);
+// Blocks per CU by registers of the kernel that runs a tile shape on a grid.
+int tile_blocks_per_cu(const pond_params &p, int tile);
 // LDS nodes per block of the tiled kernel's default share for a tile shape.
 int default_lds_nodes(int tile, const pond_params &p);
 // Default launch configuration of a context with these parameters (on the
