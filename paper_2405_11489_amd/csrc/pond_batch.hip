@@ -211,7 +211,7 @@ struct pond_batch {
     int np, split;
     hipStream_t stream;
     bool own_stream;
-    std::vector<int> order;    // the member at each place of the device tables
+    std::vector<int> place;    // each member's place in the device tables
     void *dev;  // [members | tile offsets per XCD | block offsets | flags]
     BatchMember *d_mem;
     int *d_xcd_off, *d_blk_off;
@@ -404,13 +404,15 @@ pond_status pond_batch_create(pond_ctx *const *ctxs, int n, void *hip_stream, po
     int *boff = reinterpret_cast<int *>(desc.data() + mem_bytes + xcd_bytes);
     b->parity0.resize(n);
     b->widths.resize(n);
-    b->order.resize(n);
-    std::iota(b->order.begin(), b->order.end(), 0);
-    std::stable_sort(b->order.begin(), b->order.end(),
+    b->place.resize(n);
+    std::vector<int> order(n);  // the member at each place of the device tables
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(),
                      [&](int i, int j) { return ctxs[i]->reach > ctxs[j]->reach; });
     long long tiles = 0, blocks = 0, nodes = 0;
     for (int k = 0; k < n; ++k) {
-        const int i = b->order[k];
+        const int i = order[k];
+        b->place[i] = k;
         pond_ctx *c = ctxs[i];
         const int w = member_width(c), lg = lg2(w), h = kBatchThreads >> lg;
         const int tx = (c->p.nx + w - 1) / w, ty = (c->p.ny + h - 1) / h;
@@ -553,11 +555,12 @@ pond_status pond_batch_synchronize(pond_batch *b) {
     if (e != hipSuccess) return hip_fail(e, "batch flags");
     int bad = 0;
     pond_status first = POND_OK;
-    for (size_t i = 0; i < n; ++i) {
-        pond_ctx *c = b->members[b->order[i]];
+    for (size_t i = 0; i < n; ++i) {  // in the members' order: the first failure's status
+        pond_ctx *c = b->members[i];
+        const MemberFlags &f = b->flags[b->place[i]];
         DevCounters h{};
-        h.nonphysical = b->flags[i].nonphysical;
-        h.ghost_overrun = b->flags[i].ghost_overrun;
+        h.nonphysical = f.nonphysical;
+        h.ghost_overrun = f.ghost_overrun;
         pond_status s = counters_status(c, h);
         if (s != POND_OK) {
             if (first == POND_OK) first = s;
