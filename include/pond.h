@@ -386,7 +386,8 @@ typedef struct {
     int32_t lds_nodes;    /* LDS capacity per block, in nodes */
     int64_t nodes;        /* nodes per batched step, all members */
     int64_t steps;        /* batched steps enqueued since creation */
-    int32_t graph_steps;  /* steps per captured graph (walled members) */
+    int32_t graph_steps;  /* steps per captured graph; 0 without walled members, whose
+                             steps are launched directly */
     int32_t reserved;
 } pond_batch_info_t;
 

@@ -14,7 +14,10 @@
 // those batches replay kGraphSteps steps from a captured HIP graph, one per
 // starting parity.  The others launch each step directly: a launch costs the host
 // 3.5 us, less than the smallest step takes, while the first launch of a graph
-// costs 40 us and its capture more, which a server pays at every regrouping.
+// costs 40 us and its capture more, which a server pays at every regrouping.  Nor
+// does a replay win over many steps: calls of 1 to 1000 steps of one 400 x 1 tube, one
+// 16^2 or 64^2, eight 128^2 and 64 mixed instances took the same time or up to 4 %
+// more from graphs (the tube's 1000 steps 19.4 us each against 18.8).
 //
 // (A persistent variant -- a fixed grid pulling tiles from per-XCD atomic
 // queues -- ran 2.4x slower on one 512 x 512 instance: same-address
@@ -581,7 +584,7 @@ pond_status pond_batch_get_info(pond_batch *b, pond_batch_info_t *out) {
     out->lds_nodes = b->cap;
     out->nodes = b->nodes;
     out->steps = b->steps;
-    out->graph_steps = kGraphSteps;
+    out->graph_steps = b->walled ? kGraphSteps : 0;
     out->reserved = 0;
     return POND_OK;
 }

@@ -100,3 +100,18 @@ def test_walled_batch_replays_either_parity(prec):
         pond.pond_batch_destroy(b)
         for s in sols:
             s.close()
+
+
+def test_batch_info_names_the_graph_in_use():
+    """Walled batches replay graphs of several steps, the others launch each step."""
+    from paper_2405_11489_amd import pond
+    for ws, walled in (([workloads.thermal_couette(ny=24, nx=6)], True),
+                       ([workloads.sod_tube(nx=100)], False)):
+        sols = _solvers(ws, FP32)
+        b = pond.pond_batch_create([s.ctx for s in sols])
+        try:
+            assert (pond.pond_batch_get_info(b).graph_steps > 0) == walled
+        finally:
+            pond.pond_batch_destroy(b)
+            for s in sols:
+                s.close()
