@@ -268,6 +268,10 @@ POND_API pond_status pond_import_prev_frame(pond_ctx *c, const double *prev);
  *              outside the staged region read HBM.  At most 159 KiB: one KiB of the CU's 160 stays for
  *              the kernels' static shared memory.
  *   batch_tile_width: tile of this context when it steps inside a pond_batch.
+ * Until it is set here or by pond_autotune, the configuration follows the state:
+ * pond_init_fields and pond_import_state choose it anew, from the autotuned class of
+ * the loaded frame or by its stencil reach and temperature, so pond_get_tuning may
+ * answer differently before and after them.
  * pond_set_tuning validates the values (POND_ERR_INVALID_ARG otherwise);
  * lds_nodes <= 0 selects the default for the tile.  Refused (POND_ERR_STATE)
  * while the context is a member of a batch. */

@@ -181,8 +181,8 @@ pond_tuning default_tuning(const pond_params &p, int reach, double thermal_reach
     }
     // flows whose stencils reach two nodes at most (cold, slow): small tiles, which
     // carry little more halo there and end their waves sooner where the
-    // predictor-corrector work varies (2048^2 quadrants, FP32: 0.70 ms per step
-    // against 0.81 with 32 x 8; 1024^2, FP64: 0.55 against 0.62)
+    // predictor-corrector work varies (2048^2 quadrants, FP32: 0.73 ms per step
+    // against 0.75 with 32 x 8; 1024^2, FP64: 0.55 against 0.62)
     const bool small = reach > 0 && reach <= 2 && p.ny >= 16;
     // D2Q25: square tiles, whose source regions carry less halo per node (512^2
     // Mach 2: 545 against 495 MLUPS with 32 x 8)
@@ -333,8 +333,8 @@ pond_status apply_tuning(pond_ctx *c, const pond_tuning &t) {
     if (bytes > 159 * 1024)  // one KiB stays for the static shared memory
         return fail(POND_ERR_INVALID_ARG, "lds_nodes %d needs %zu bytes of LDS (> 159 KiB)",
                     u.lds_nodes, bytes);
-    const int h = halo_for(u.tile, u.lds_nodes, c->p.ny == 1);
-    if (h < 0) return fail(POND_ERR_INVALID_ARG, "lds_nodes %d smaller than the tile", u.lds_nodes);
+    if (halo_for(u.tile, u.lds_nodes, c->p.ny == 1) < 0)
+        return fail(POND_ERR_INVALID_ARG, "lds_nodes %d smaller than the tile", u.lds_nodes);
     if (u.batch_tile_width != 0 && u.batch_tile_width != 16 && u.batch_tile_width != 32 &&
         u.batch_tile_width != 64 && u.batch_tile_width != 128 && u.batch_tile_width != 256)
         return fail(POND_ERR_INVALID_ARG, "batch_tile_width %d not in {0, 16, 32, 64, 128, 256}",
@@ -342,7 +342,6 @@ pond_status apply_tuning(pond_ctx *c, const pond_tuning &t) {
     c->tuning = u;
     c->tc.shape = static_cast<TileShape>(u.tile);
     c->tc.cap = u.lds_nodes;
-    c->tc.halo_cap = h;
     return POND_OK;
 }
 

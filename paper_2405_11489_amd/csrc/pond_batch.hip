@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kBatchThreads) void batch_moments_kernel(
 // xcd_off: per XCD x the offsets [x (nmem + 1) + i] of member i's tiles in its list.
 template <typename P, int NP, int S, class L>
 __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(
-    step_min_waves<P, S, kBatchThreads, L>()))) void batch_step_kernel(
+    step_min_waves<P>()))) void batch_step_kernel(
     const BatchMember *__restrict__ mem, const int *__restrict__ xcd_off, int nmem, int cap,
     int flip) {
     extern __shared__ __align__(16) unsigned char smem_raw[];

@@ -75,14 +75,13 @@ struct StepArgs {
 };
 
 // Tiled step launch configuration: block shape, LDS capacity (nodes of the
-// staged source region) and the largest halo that fits it.
+// staged source region).
 enum class TileShape : int { T16x16 = 0, T32x8 = 1, T16x8 = 2, T8x8 = 3, T256x1 = 4, T64x1 = 5,
                              T32x16 = 6 };
 
 struct TileConfig {
     TileShape shape;
-    int cap;       // nodes of LDS per block
-    int halo_cap;  // largest symmetric halo h with (TX + 2h)(TY + 2h) <= cap (>= 0: the tile fits)
+    int cap;  // nodes of LDS per block
 };
 
 inline void tile_dims(TileShape s, int &tx, int &ty) {
@@ -109,7 +108,8 @@ inline void tile_dims(TileShape s, int &tx, int &ty) {
 // 64^2 0.035 / 0.094 and 0.034 / 0.086, 160^2 0.067 / 0.094 and 0.060 / 0.088,
 // 192^2 0.086 / 0.101 and 0.072 / 0.089, 256^2 0.113 / 0.084 and 0.102 / 0.089.
 inline bool quad_lanes(long long N, bool dbl) { return N <= (dbl ? 36864 : 49152); }
-// Blocks per CU of the four-lane kernels by registers (the LDS share of a block).
+// Blocks per CU of the four-lane kernels by registers (the LDS share of a block); the
+// FP64 quadratic one would fit twice, but keeps the whole LDS as the cubic one does.
 inline int quad_blocks_per_cu(bool dbl) { return dbl ? 1 : 2; }
 
 // Blocks of a kernel per CU by registers and static LDS.  A property of the built

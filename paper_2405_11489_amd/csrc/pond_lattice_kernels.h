@@ -114,12 +114,12 @@ __global__ __launch_bounds__(kBlock) void step_kernel(StepArgs a, DevState src,
 #ifndef POND_TILED_WAVES_PER_EU
 #define POND_TILED_WAVES_PER_EU 0
 #endif
-#define POND_TILED_ATTR(P, S, NT, L)                                                     \
+#define POND_TILED_ATTR(P)                                                                   \
     __attribute__((amdgpu_waves_per_eu(POND_TILED_WAVES_PER_EU > 0 ? POND_TILED_WAVES_PER_EU \
-                                                                   : step_min_waves<P, S, NT, L>())))
+                                                                   : step_min_waves<P>())))
 
 template <typename P, int NP, int S, class L, int TX, int TY>
-__global__ __launch_bounds__(TX *TY) POND_TILED_ATTR(P, S, TX *TY, L) void step_tiled_kernel(StepArgs a, DevState src,
+__global__ __launch_bounds__(TX *TY) POND_TILED_ATTR(P) void step_tiled_kernel(StepArgs a, DevState src,
                                                             const P *__restrict__ mom,
                                                             DevState dst, P *__restrict__ mom_out,
                                                             DevCounters *cnt, int cap, int tiles_x) {
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(TX *TY) POND_TILED_ATTR(P, S, TX *TY, L) void step_
 // Four lanes per node (node_step's Quad): blocks of 64 nodes, 8 x 8 or 64 x 1, 256
 // lanes.
 template <typename P, int NP, int S, class L, int TX, int TY>
-__global__ __launch_bounds__(4 * TX * TY) POND_TILED_ATTR(P, S, 4 * TX * TY, L) void step_quad_kernel(
+__global__ __launch_bounds__(4 * TX * TY) POND_TILED_ATTR(P) void step_quad_kernel(
     StepArgs a, DevState src, const P *__restrict__ mom, DevState dst, P *__restrict__ mom_out,
     DevCounters *cnt, int cap, int tiles_x) {
     extern __shared__ __align__(16) unsigned char smem_raw[];

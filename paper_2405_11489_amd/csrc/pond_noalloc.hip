@@ -124,9 +124,6 @@ pond_status pond_step_noalloc(const pond_params *p, const double *u_ref, void *f
     TileConfig tc;
     tc.shape = static_cast<TileShape>(t.tile);
     tc.cap = t.lds_nodes;
-    int tx = 0, ty = 0;
-    tile_dims(tc.shape, tx, ty);
-    tc.halo_cap = halo_for_dims(tx, ty, tc.cap, p->ny == 1);
 
     char *base = static_cast<char *>(ws);
     DevCounters *cnt = reinterpret_cast<DevCounters *>(base);

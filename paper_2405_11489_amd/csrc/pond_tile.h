@@ -101,12 +101,11 @@ __device__ __forceinline__ void block_bounds(int (&v)[4], int *red) {
     }
 }
 
-// Minimum waves per SIMD asked of the register allocator for the step kernels of
-// NT lanes per block.  FP32 needs nearly 256 VGPRs: two waves (three, at 168 VGPRs,
+// Minimum waves per SIMD asked of the register allocator for the step kernels.  FP32 needs nearly 256 VGPRs: two waves (three, at 168 VGPRs,
 // spill 36 of them: 2048^2 quadrants 0.82 against 0.71 ms per step, 512^2 Mach 2
 // 0.117 against 0.113).  FP64 holds the weight table and a row in twice the
 // registers: one wave of 512 (two spill 130: 512^2 Mach 2 0.51 against 0.34 ms).
-template <typename P, int S, int NT = 256, class L = D2Q16>
+template <typename P>
 constexpr int step_min_waves() {
     return sizeof(P) == 4 ? 2 : 1;
 }
