@@ -71,50 +71,56 @@ CANON_BYTES_FP32 = 2 * (128 + 24)
 CANON_BYTES_FP64 = 2 * (256 + 24)
 
 
-# A count of the flops per node-update in interpolate-then-transform form with a
-# coefficient vector per velocity (the step kernel reduces each stencil row to N + 1
-# numbers per distribution first and performs fewer):
-#   per predictor-corrector iteration: departure points and weights 112,
-#   interpolation 16 velocities x NP^2 taps x (1 weight product + 20 moments x
-#   FMA) = 10496 for the cubic stencil (NP = 4), 5904 for the quadratic one,
-#   frame transformation 16 velocities x 2 distributions x 65 = 2080;
+# The flops per node-update that the step kernel performs (an FMA counts two):
+#   per predictor-corrector gather (gather_rows): departure points and row weights
+#   112 (D2Q25 175), then for each x-component of Q1 velocities
+#     - per row of the union of their row stencils: interpolation of 2 NM moments over
+#       NP columns, the reduction to the N + 1 numbers per distribution, and their sum
+#       into the Q1 populations of f and of g;
+#     - once: column weights, x-factors, and the FP64 and lattice sums of the
+#       populations;
 #   once per node: moments of the gathered populations 784, re-projection 110,
 #   collision 60, reconstruction 640, and the moments of the stored populations
-#   for the next step 784 (the step kernel writes them; no separate pre-pass).
-# D2Q25 (Grad order 4, 15 moments per distribution), same accounting: per
-# iteration departure points 175, interpolation 25 x NP^2 x (1 + 15 x 4),
-# transformation 25 x 2 x 85 (30 FMAs and the shared order-4 shift/scale);
-# once per node 1850 + 250 + 80 + 1500 + 1850.
+#   for the next step 784 (D2Q25 1850 + 250 + 80 + 1500 + 1850).
+# Without a row count, flops_per_iter gives the interpolate-then-transform form with a
+# coefficient vector per velocity: points 112, 16 velocities x NP^2 taps x (1 weight
+# product + 20 moments x FMA), frame transformation 16 x 2 x 65; D2Q25 175, 25 x NP^2 x
+# (1 + 15 x 4), 25 x 2 x 85.
 def flops_per_iter(np_, q=16, shared_rows=None):
-    """Per predictor-corrector gather.  shared_rows: the FP32 D2Q16 kernel's
-    mean rows per x-pass (the union of the four row stencils of an
-    x-component, see shared_rows_mean); per x-component it interpolates that
-    many rows along x (NP taps x 20 moments, FMA), and each velocity takes its
-    NP rows through its coefficients (20 FMA + 1 per row); per velocity the
-    coefficients (45); once, the reference moments' share of the sums (30).
-    D2Q25 (q = 25): the per-velocity count (30 moments at NP^2 taps for each
-    of the 25 velocities), the D2Q25 form of the canonical count; its FP32
-    kernel shares the x-pass, which this count takes as speed."""
-    if q == 25:
-        return 175 + 25 * np_ * np_ * 61 + 4250
-    if shared_rows is not None:
-        return 112 + 4 * (shared_rows * np_ * 20 * 2) + 16 * np_ * 21 * 2 + 16 * 45 + 30
-    return 112 + 16 * np_ * np_ * 41 + 2080
+    """Per predictor-corrector gather; shared_rows: mean rows of an x-component's
+    union (shared_rows_mean)."""
+    if shared_rows is None:
+        if q == 25:
+            return 175 + 25 * np_ * np_ * 61 + 4250
+        return 112 + 16 * np_ * np_ * 41 + 2080
+    q1, n = (5, 4) if q == 25 else (4, 3)
+    nm = (n + 1) * (n + 2) // 2
+    # row_factors: sum of l over the (p, l) with p + l <= n, then their products
+    shift = sum(l * (n - l + 1) for l in range(1, n + 1))
+    factors = 2 * (shift + n * (n + 1) // 2 + 1) + n
+    # add_row: even and odd part of a pair, both populations, and the zero abscissa
+    add = (q1 // 2) * 2 * (n // 2 + (n - 1) // 2 + 4) + (6 if q1 % 2 else 0)
+    row = np_ * 2 * nm * 2 + 2 * (factors + add)
+    sums = 6 * q1 + 2 * (q1 + 2 * (n + 1) * (q1 // 2)) + 4 * nm
+    component = 20 + n * (n + 1) + 2 * nm + sums
+    return (175 if q == 25 else 112) + q1 * (shared_rows * row + component)
 
 
-def shared_rows_mean(w, np_=4):
-    """Mean rows per x-pass of the shared gather over the workload's initial
-    frames: the union of the row stencils of the four y-departures
-    y - u_y - sqrt(T) c_b (cubic: floor - 1 .. floor + 2), or the four separate
-    stencils (4 NP rows) where the union is longer."""
-    c_out = 2.3344142183389773
+def shared_rows_mean(w, np_=4, q=16):
+    """Mean rows per x-component of the gather over the workload's initial
+    frames: the union of the row stencils of the Q1 y-departures
+    y - u_y - sqrt(T) c_b (cubic: floor - 1 .. floor + 2), or the separate
+    stencils (Q1 NP rows) where the union is longer; one on a single-row grid."""
+    c_out = 2.8569700138728056 if q == 25 else 2.3344142183389773
+    if w.ny == 1:
+        return 1.0
     yy = np.arange(w.ny, dtype=np.float64)[:, None] - w.uy
     s = np.sqrt(w.T)
     if np_ == 4:
         span = np.floor(yy + s * c_out) - np.floor(yy - s * c_out) + 4
     else:
         span = np.floor(yy + s * c_out + 0.5) - np.floor(yy - s * c_out + 0.5) + 3
-    return float(np.mean(np.minimum(span, 4 * np_)))
+    return float(np.mean(np.minimum(span, (5 if q == 25 else 4) * np_)))
 
 
 def flops_per_node(q=16):
@@ -601,11 +607,15 @@ def roofline(m, N, prec, interp_points, lattice, split, kname, traffic, shared_r
             **extra}
 
 
-def kernel_name(m, prec, interp_points, split, lattice, kernel):
+def kernel_name(m, prec, interp_points, split, lattice, kernel, nodes):
     ptype = "float" if prec == "fp32" else "double"
     lat = f"D2Q{lattice}"
     if kernel == "tiled":
-        return f"step_tiled_kernel<{ptype},{interp_points},{split},{lat},{TILE_DIMS[m['tuning'].tile]}>"
+        # 64-node tiles of small D2Q16 grids: four lanes per node
+        quad = (lattice == 16 and m["tuning"].tile in (3, 5)
+                and nodes <= (49152 if prec == "fp32" else 36864))
+        return (f"step_{'quad' if quad else 'tiled'}_kernel<{ptype},{interp_points},{split},{lat},"
+                f"{TILE_DIMS[m['tuning'].tile]}>")
     return f"step_kernel<{ptype},{interp_points},{split},{lat}>"
 
 
@@ -729,9 +739,9 @@ def main():
         f"warmup {args.warmup}, steps {args.steps}")
     m = measure(pond, torch, w, args, prec, split, args.lattice, args.interp_points, tuning,
                 autotune=autotune)
-    kname = kernel_name(m, args.precision, args.interp_points, split, args.lattice, args.kernel)
-    shared = (shared_rows_mean(w, args.interp_points)
-              if args.precision == "fp32" and args.lattice == 16 else None)
+    kname = kernel_name(m, args.precision, args.interp_points, split, args.lattice, args.kernel,
+                        w.nodes)
+    shared = shared_rows_mean(w, args.interp_points, args.lattice)
     roof = roofline(m, w.nodes, args.precision, args.interp_points, args.lattice, split, kname,
                     traffic_record(kname, args.precision, wname), shared)
     log(f"time {m['ms']:.1f} ms (host {m['wall_s'] * 1e3:.1f} ms), {m['mlups']:.1f} MLUPS, "
@@ -762,9 +772,8 @@ def main():
         m2 = measure(pond, torch, w2, args, prec, split, args.lattice, args.interp_points, tuning,
                      autotune=autotune)
         kname2 = kernel_name(m2, args.precision, args.interp_points, split, args.lattice,
-                             args.kernel)
-        shared2 = (shared_rows_mean(w2, args.interp_points)
-                   if args.precision == "fp32" and args.lattice == 16 else None)
+                             args.kernel, w2.nodes)
+        shared2 = shared_rows_mean(w2, args.interp_points, args.lattice)
         r2 = roofline(m2, w2.nodes, args.precision, args.interp_points, args.lattice, split,
                       kname2, traffic_record(kname2, args.precision, wname2), shared2)
         extras["mach2_fourier_modes_512x512"] = {
