@@ -428,14 +428,14 @@ __device__ __forceinline__ void gather_rows(const Taps &taps, double xu, double 
     const int x1 = stencil_base<NP>(fma(-sc, L::c(0), xu));
     const bool fits = span <= RS && taps.inside(x0, x1 + NP - x0, r0, span);
     // How likely the unrolled rows are, for the register allocator: it takes the loops
-    // of the other path for the hot ones and spills here for them unless told (2048^2
-    // quadrants 0.77 ms per step, 0.73 when told; hot flows of T = 4 0.164 and 0.174 of
-    // 512^2).  In FP64 the surer it is the more it spills there (D2Q16 512^2 0.30 when
-    // sure, 0.28 so, T = 4 0.52 and 0.48), and on D2Q25 in any case (400^2 0.43 untold,
-    // 0.48 so).
+    // of the other path for the hot ones and spills here for them unless told, in FP32
+    // strongly (2048^2 quadrants 0.77 ms per step untold, 0.73 here, 24 % more bytes
+    // written at the usual 0.9995; hot flows of T = 4 0.164 and 0.174 of 512^2).  In
+    // FP64 the surer it is the more it spills here (D2Q16 512^2 0.30 when sure, 0.28 so,
+    // T = 4 0.52 and 0.48), and on D2Q25 in any case (400^2 0.43 untold, 0.48 so).
     const bool unroll = __ballot(!fits) == 0;
     if (Taps::kStaged &&
-        (sizeof(P) == 4 ? __builtin_expect(unroll, 1)
+        (sizeof(P) == 4 ? __builtin_expect_with_probability(unroll, 1, 0.999999)
                         : L::Q == 25 ? unroll
                                      : __builtin_expect_with_probability(unroll, 1, 0.99))) {
         P wt[RS][Q1];
